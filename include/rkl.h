@@ -259,7 +259,7 @@ rkl_status rkl_supersteps_async(rkl_plan_t plan, int32_t grid, double *T, const 
  * Limits: at most RKL_NOALLOC_MAX_CELLS cells and s_cap in [2,
  * RKL_NOALLOC_MAX_STAGES]; larger requests return RKL_EINVAL with a message.
  * s_out: device int32 (may be NULL) receiving s; if s > s_cap, T is left
- * unchanged (s_out tells).  Stencil variant 0.  Every call on one GPU shares
+ * unchanged (s_out tells).  The default stencil variant.  Every call on one GPU shares
  * that GPU's scratch, so calls that overlap on one GPU (two streams or host
  * threads at once) race; serialise them.
  */
@@ -331,8 +331,8 @@ rkl_status rkl_query(rkl_plan_t plan, int32_t grid, int32_t *last_s, double *las
 
 /*
  * Stencil kernel variants: rkl_variant_count() of them.  rkl_variant_info
- * fills the workgroup tile (tile_x x tile_y cells, a z-chunk of tile_z
- * planes) and the stages per launch `fuse` (any pointer may be NULL):
+ * fills the workgroup tile (tile_x x tile_y cells, z-chunks of at most tile_z
+ * planes; a grid too small to fill the GPU with them takes shorter ones) and the stages per launch `fuse` (any pointer may be NULL):
  *   fuse 1: one RKL2 stage per launch, output tile = tile_x x tile_y;
  *   fuse F = 2, 3, 4: stages j..j+F-1 in one launch (temporal fusion of
  *           Appendix A's recurrence; 2 <= j, j+F-1 < s; the last stage, and a

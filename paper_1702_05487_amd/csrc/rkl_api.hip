@@ -34,7 +34,7 @@ struct rkl_plan_s {
     int device = 0;
     int ngrids = 0;
     int precision = RKL_FP64;
-    int variant = 0;
+    int variant = kDefaultVariant;
     int smax = 1024;
     int scheme = RKL_RKL2;
     std::vector<rkl_grid_desc> desc;
@@ -418,7 +418,7 @@ rkl_status rkl_plan(const rkl_grid_desc* grids, int32_t ngrids, const rkl_option
     rkl_plan_s* p = new rkl_plan_s();
     p->ngrids = ngrids;
     p->precision = o.precision;
-    p->variant = 0;
+    p->variant = kDefaultVariant;
     p->smax = o.smax;
     p->scheme = o.scheme;
     p->off.push_back(0);
@@ -442,7 +442,8 @@ rkl_status rkl_plan(const rkl_grid_desc* grids, int32_t ngrids, const rkl_option
     int64_t ext_blocks = 1;
     for (int32_t g = 0; g < ngrids; ++g)
         for (int v = 0; v < variant_count(); ++v)
-            if (variant_get(v).fuse == 1) ext_blocks = std::max(ext_blocks, stage_blocks(variant_get(v), p->gc[g]));
+            if (variant_get(v).fuse == 1)
+                ext_blocks = std::max(ext_blocks, stage_blocks(fit_variant(p->precision, variant_get(v), p->gc[g]), p->gc[g]));
     bool ok = hipMalloc(&p->Ya, sizeof(double) * p->total) == hipSuccess &&
               hipMalloc(&p->Yb, sizeof(double) * p->total) == hipSuccess &&
               hipMalloc(&p->MY0, rs * p->total) == hipSuccess &&
@@ -470,7 +471,7 @@ rkl_status rkl_plan(const rkl_grid_desc* grids, int32_t ngrids, const rkl_option
         rkl_status st = batch_create(p->desc, p->gc, p->off, p->precision, p->smax, 0, &p->batch, why);
         if (st != RKL_OK) { free_plan(p); return fail(st, why); }
     }
-    if (o.variant > 0) {
+    if (o.variant >= 0) {
         rkl_status st = select_variant(p, o.variant);
         if (st != RKL_OK) {
             const std::string why = g_err;
@@ -521,6 +522,18 @@ static rkl_status check_grid(rkl_plan_t p, int32_t g) {
     return RKL_OK;
 }
 
+// the plan's variant as a one-stage launch on grid g runs it
+static Variant fitted(rkl_plan_t p, int32_t g) {
+    return fit_variant(p->precision, variant_get(p->variant), p->gc[g]);
+}
+
+// the same for routed launches, which are one stage each (variant 0 while a
+// variant of several stages is selected)
+static Variant routed(rkl_plan_t p, int32_t g) {
+    const Variant v = variant_get(p->variant);
+    return fit_variant(p->precision, v.fuse == 1 ? v : variant_get(0), p->gc[g]);
+}
+
 // min/max reduction of T and the finalize step for grid g
 static rkl_status reduce_and_finalize(rkl_plan_t p, int32_t g, const double* T, double dt_hyp, int mode,
                                       int32_t* s_dev, hipStream_t st, int smax = 0) {
@@ -541,7 +554,7 @@ rkl_status rkl_flux_div(rkl_plan_t p, int32_t g, const double* T, const void* b,
     hipStream_t s = (hipStream_t)stream;
     st = reduce_and_finalize(p, g, T, 0.0, 1, nullptr, s);
     if (st != RKL_OK) return st;
-    HIPCHECK(launch_stage(p->precision, variant_get(p->variant), p->gc[g], 0, 0, T, nullptr, nullptr, nullptr, nullptr,
+    HIPCHECK(launch_stage(p->precision, fitted(p, g), p->gc[g], 0, 0, T, nullptr, nullptr, nullptr, nullptr,
                           out, b, p->state + g, p->coef, s),
              "flux_div launch");
     return RKL_OK;
@@ -582,7 +595,7 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
                                      ", smax=" + std::to_string(p->smax) + "]");
 
     const GridConst& gc = p->gc[g];
-    const Variant v = variant_get(p->variant);
+    const Variant v = variant_get(p->variant), v1 = fitted(p, g);
     const int64_t n = p->off[g + 1] - p->off[g];
     double* bufs[4] = {p->Ya + p->off[g], p->Yb + p->off[g], p->Yc ? p->Yc + p->off[g] : nullptr,
                        p->Yd ? p->Yd + p->off[g] : nullptr};
@@ -590,7 +603,7 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
     void* M = (char*)p->MY0 + rs * p->off[g];
     const GridState* gs = p->state + g;
     // stage 1: Y1 = Y0 + mut_1 tau M(Y0), tau M(Y0) kept for the later stages
-    HIPCHECK(launch_stage(p->precision, v, gc, 1, 1, T, nullptr, nullptr, nullptr, M, bufs[0], b, gs, p->coef, s),
+    HIPCHECK(launch_stage(p->precision, v1, gc, 1, 1, T, nullptr, nullptr, nullptr, M, bufs[0], b, gs, p->coef, s),
              "stage 1 launch");
     // a stage buffer holding neither Y_{j-1} nor Y_{j-2}
     auto pick = [&](const double* u, const double* w, const double* x) -> double* {
@@ -629,7 +642,7 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
         } else {
             // Y_j overwrites Y_{j-2} cell by cell (never Y0 = T before the last stage)
             double* out = j == S ? T : (ym2 == T ? pick(ym1, T, nullptr) : const_cast<double*>(ym2));
-            HIPCHECK(launch_stage(p->precision, v, gc, 2, j, ym1, ym2, T, M, nullptr, out, b, gs, p->coef, s),
+            HIPCHECK(launch_stage(p->precision, v1, gc, 2, j, ym1, ym2, T, M, nullptr, out, b, gs, p->coef, s),
                      "stage launch");
             ym2 = ym1;
             ym1 = out;
@@ -663,8 +676,7 @@ rkl_status rkl_superstep_async(rkl_plan_t p, int32_t g, double* T, const void* b
     st = reduce_and_finalize(p, g, T, dt_hyp, 0, s_out, s, s_cap);
     if (st != RKL_OK) return st;
     const GridConst& gc = p->gc[g];
-    Variant v = variant_get(p->variant);
-    if (v.fuse != 1) v = variant_get(0);   // routed launches are one stage each
+    const Variant v = routed(p, g);
     const size_t rs = p->precision == RKL_MIXED ? sizeof(float) : sizeof(double);
     void* M = (char*)p->MY0 + rs * p->off[g];
     const Route r{p->Ya + p->off[g], p->Yb + p->off[g], s_cap, 0};
@@ -689,8 +701,7 @@ rkl_status rkl_supersteps_async(rkl_plan_t p, int32_t g, double* T, const void* 
     if (nsteps < 1) return fail(RKL_EINVAL, "nsteps must be >= 1");
     hipStream_t s = (hipStream_t)stream;
     const GridConst& gc = p->gc[g];
-    Variant v = variant_get(p->variant);
-    if (v.fuse != 1) v = variant_get(0);   // routed launches are one stage each
+    const Variant v = routed(p, g);
     // the compile-time-shaped stage kernels keep the last stage's extrema;
     // other grids take the reduction pass before every super-step
     const bool keep = gc.ndim == 3 && !gc.fixed;
@@ -724,7 +735,7 @@ rkl_status rkl_supersteps_async(rkl_plan_t p, int32_t g, double* T, const void* 
 static rkl_status euler_substeps(rkl_plan_t p, int32_t g, double* T, const void* b, int64_t count,
                                  const std::function<double(int64_t)>& tau, hipStream_t s) {
     const GridConst& gc = p->gc[g];
-    const Variant v = variant_get(p->variant);
+    const Variant v = fitted(p, g);
     const int64_t n = p->off[g + 1] - p->off[g];
     double* A = p->Ya + p->off[g];
     for (int64_t k = 0; k < count; ++k) {

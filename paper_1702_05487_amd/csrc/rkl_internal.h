@@ -115,6 +115,10 @@ struct Variant {
 };
 int variant_count();
 Variant variant_get(int v);
+constexpr int kDefaultVariant = 1;   // 32 x 8 tile, z-chunks of at most 64 planes
+// the variant as a one-stage launch on grid gc runs it: its z-chunk shortened
+// where the grid would leave CUs idle, the 16 x 16 tile for fixed axes
+Variant fit_variant(int precision, Variant v, const GridConst& gc);
 
 // Launchers (enqueue only; return the HIP error of the launch).
 // skip (may be NULL): when *skip is nonzero on the device the launch does
@@ -155,12 +159,13 @@ struct ExtOut {
     double* part;
     int32_t* ok;
 };
-// workgroups of a one-stage launch of variant v on grid gc
+// workgroups of a one-stage launch of (fitted) variant v on grid gc
 int64_t stage_blocks(Variant v, const GridConst& gc);
 // kind: 0 flux divergence into Yout, 1 first stage, 2 stage j >= 2,
 // 3 explicit sub-step Yout = Yin + tau L(Yin) with sub_scale = -tau (gamma-1)/rho.
 // With `route` set (kinds 1 and 2), Yin, Ym2 and Yout are chosen on the
-// device as described above and the ones passed are ignored.
+// device as described above and the ones passed are ignored.  v: fitted to
+// the grid by fit_variant.
 hipError_t launch_stage(int precision, Variant v, const GridConst& gc, int kind, int stage,
                         const double* Yin, const double* Ym2, const double* Y0, const void* MY0in,
                         void* MY0out, double* Yout, const void* b, const GridState* state,

@@ -3,6 +3,9 @@
 // dt_par, the stage count s and the stage scale (Sec. 3.1 Eq. dt_exp,
 // Sec. 3.3 Eq. RKL-s, Sec. 4.1 rounding), and the stencil/stage kernels that
 // wrap run_tile (rkl_tile.h).
+#include <algorithm>
+#include <cmath>
+
 #include "rkl_stage.h"
 
 namespace rkl {
@@ -147,8 +150,52 @@ static hipError_t launch_prec(const StageLaunch& P, int nblocks, int bx, int by,
     return hipErrorInvalidValue;
 }
 
+// Planes per workgroup of a one-stage launch on a 3-D grid.  A workgroup
+// marches its z-chunk plane after plane, each plane a chain of one barrier,
+// LDS exchanges and three face evaluations, so a launch takes as long as its
+// longest march times the rounds of resident workgroups.  A chunk of bz
+// planes costs bz + 2 plane iterations (the two before z0 fill the rings);
+// an iteration takes c[k] microseconds with k workgroups on a CU (MC, T^2.5
+// and saturated flux; measured with 64^3 to 192^3 grids, k = 1, 2, 3; three
+// mixed or two FP64 workgroups fit a CU's registers).  Short chunks give a
+// small grid enough workgroups for the 256 CUs, long ones keep the two extra
+// iterations and the halo planes cheap.  Measured per stage, 32 x 8 tile,
+// the variant's own 32 planes against the chunk taken here: 45 x 33 x 29 FP64
+// 37.8 -> 8.8 us, 64^3 mixed 38.0 -> 8.8 us, 128^3 FP64 50.7 -> 39.3 us,
+// 150 x 127 x 101 mixed 45.2 -> 28.9 us.  The last, partly filled round is
+// priced half by its share of the slots and half as a round of its own:
+// workgroups of different rounds overlap, but not fully.
+Variant fit_variant(int precision, Variant v, const GridConst& gc) {
+    if (gc.fixed) v = Variant{16, 16, v.bz, 1};   // the tile shape of the ghost-loading kernel
+    if (gc.n2 == 1) return v;
+    const int per_cu = precision == RKL_MIXED ? 3 : 2;
+    static const double c32[] = {0.0, 1.03, 1.3, 1.6}, c64[] = {0.0, 1.3, 1.95};
+    const double* c = precision == RKL_MIXED ? c32 : c64;
+    const int64_t tiles = (int64_t)((gc.n0 + v.bx - 1) / v.bx) * ((gc.n1 + v.by - 1) / v.by);
+    const int64_t slots = 256 * per_cu;
+    int best = v.bz;
+    double best_cost = INFINITY;
+    for (int z = std::min(v.bz, gc.n2); z >= 1; --z) {
+        const int nzc = (gc.n2 + z - 1) / z;
+        const int bz = (gc.n2 + nzc - 1) / nzc;   // chunks of equal length
+        if (bz != z) continue;
+        const int64_t nb = tiles * nzc, full = nb / slots, rem = nb % slots;
+        double rounds = (double)full;
+        if (rem) {
+            const double share = (double)rem / slots, own = c[(rem + 255) / 256] / c[per_cu];
+            rounds += full ? 0.5 * (share + own) : own;
+        }
+        const double cost = (bz + 2) * rounds;
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = bz;
+        }
+    }
+    v.bz = best;
+    return v;
+}
+
 int64_t stage_blocks(Variant v, const GridConst& gc) {
-    if (gc.fixed) v = Variant{16, 16, v.bz, 1};
     return (int64_t)((gc.n0 + v.bx - 1) / v.bx) * ((gc.n1 + v.by - 1) / v.by) * ((gc.n2 + v.bz - 1) / v.bz);
 }
 
@@ -157,7 +204,6 @@ hipError_t launch_stage(int precision, Variant v, const GridConst& gc, int kind,
                         void* MY0out, double* Yout, const void* b, const GridState* state,
                         const double* coef, hipStream_t st, double sub_scale, const Route* route,
                         const ExtOut* ext) {
-    if (gc.fixed) v = Variant{16, 16, v.bz, 1};   // the tile shape of the ghost-loading kernel
     StageLaunch P;
     TileArgs& a = P.t;
     a.Yin = Yin;

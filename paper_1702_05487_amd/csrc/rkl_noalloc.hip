@@ -104,8 +104,9 @@ extern "C" rkl_status rkl_superstep_noalloc(const rkl_grid_desc* grid, int32_t p
     e = launch_finalize(part, nb, gc, dt_hyp, 0, state, s_out, s_cap, s, coef);
     if (e != hipSuccess) return hipfail(e, "finalize launch");
     const Route r{A, B, s_cap, 1};
+    const Variant v = fit_variant(precision, variant_get(kDefaultVariant), gc);
     for (int j = 1; j <= s_cap; ++j) {
-        e = launch_stage(precision, variant_get(0), gc, j == 1 ? 1 : 2, j, nullptr, nullptr, nullptr, M, M, T, b,
+        e = launch_stage(precision, v, gc, j == 1 ? 1 : 2, j, nullptr, nullptr, nullptr, M, M, T, b,
                          state, coef, s, 0.0, &r);
         if (e != hipSuccess) return hipfail(e, "routed stage launch");
     }

@@ -1,0 +1,56 @@
+"""z-chunk lengths of the 3-D stage kernels on grids wide enough to keep them.
+
+A launch shortens its z-chunks while the grid would leave CUs idle, so
+narrow grids run chunks of one or two planes whatever their depth.  Here a
+plane holds 512 tiles of 32 x 8 cells, which fills the GPU, and a chunk is as
+long as the variant allows: the depths give every remainder of the six-fold
+plane loop in one chunk, and chunks of unequal work at 33 and 65 planes.
+
+  - depths to 14: against the oracle, FP64 rel-L1 <= 1e-12, mixed <= 1e-5
+    (the bars of the other super-step tests), the same stage count;
+  - every depth: the same bits with chunks of at most 16, 32 and 64 planes,
+    and from rkl_superstep_async.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import lib_desc, oracle_grid, rel_l1
+from paper_1702_05487_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+H = (0.03, 0.04, 0.05)
+
+
+@pytest.mark.parametrize("depth", (1, 2, 3, 4, 5, 6, 7, 9, 14, 33, 65))
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_long_chunks(precision, depth):
+    import torch
+    from paper_1702_05487_amd import rkl
+    print("z-chunk", precision, depth, flush=True)
+    n = (512, 256, depth)
+    rng = np.random.default_rng(2000 + depth)
+    T = 1.0 + 0.2 * rng.random((depth, 256, 512))
+    b = inputs.unit_vectors(rng.standard_normal((3, depth, 256, 512)))
+    p = dict(inputs.SPITZER_MC_SAT, phi=0.003)
+    g = oracle_grid(n, H, 3, p)
+    dt = inputs.midpoint_ratio(4) * oracle.dt_par(g, T)
+    bd = torch.from_numpy(b).to("cuda:0", torch.float32 if precision == "mixed" else torch.float64)
+    got = {}
+    for v in (6, 0, 1, 3):
+        plan = rkl.Plan([lib_desc(n, H, 3, p)], precision=precision, variant=v)
+        Td = torch.from_numpy(T).to("cuda:0")
+        assert plan.superstep(Td, bd, dt) == 4
+        Ta = torch.from_numpy(T).to("cuda:0")
+        plan.superstep_async(Ta, bd, dt, 5)
+        assert torch.equal(Td, Ta), v
+        plan.close()
+        got[v] = Td.cpu().numpy()
+        assert np.array_equal(got[v], got[6]), v
+    if depth <= 14:
+        oracle.set_threads(16)
+        ref, s, _ = oracle.superstep(g, T, bd.double().cpu().numpy(), dt)
+        oracle.set_threads(1)
+        assert s == 4
+        assert rel_l1(got[6], ref) <= (1e-12 if precision == "fp64" else 1e-5)
