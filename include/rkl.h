@@ -121,8 +121,11 @@ typedef struct {
 /*
  * rkl_plan: validate `ngrids` grid descriptors and allocate the plan's device
  * scratch (two FP64 stage buffers -- four if opt->variant is a two-stage
- * variant --, the tau*M(Y0) buffer, reduction space and the RKL2 coefficient
- * table for s = 2..smax, Appendix A).  Grids are packed back to back for the
+ * variant --, for 1-D and 2-D grids of up to 2^26 cells three more of the
+ * largest such grid, the tau*M(Y0) buffer, reduction space and the RKL2
+ * coefficient table for s = 2..smax, Appendix A).  1-D and 2-D grids run
+ * several stages per launch whatever the variant (one, if those three buffers
+ * cannot be allocated); the results have the same bits.  Grids are packed back to back for the
  * batched entry points; rkl_grid_offset gives each grid's first cell.  The
  * device current at this call is the plan's device: every later call on the
  * plan (except rkl_destroy, which switches to it) returns RKL_EINVAL while
@@ -355,7 +358,7 @@ rkl_status rkl_set_variant(rkl_plan_t plan, int32_t variant);
  * stages j >= 2 of every following rkl_superstep and (eager, not captured)
  * rkl_superstep_batched (the dominant kernels) and around each sub-step
  * launch of rkl_subcycle and rkl_aag; rkl_profile(plan, 0) stops and
- * discards.
+ * discards.  While it records, 1-D and 2-D grids run one stage per launch.
  * rkl_profile_read synchronises and returns, over the launches of one kind
  * -- `fuse` 1: one stage per launch, 2..4: that many fused stages, 5:
  * forward-Euler sub-steps, 6: the persistent batched launch (all stages of a

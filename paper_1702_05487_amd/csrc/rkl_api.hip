@@ -11,6 +11,7 @@
 #include "../../include/rkl.h"
 #include "rkl_internal.h"
 #include "rkl_batch.h"
+#include "rkl_flat.h"
 #include "rkl_host.h"
 
 using namespace rkl;
@@ -45,6 +46,12 @@ struct rkl_plan_s {
     double* Yb = nullptr;
     double* Yc = nullptr;       // two more, allocated once a two-stage variant is selected
     double* Yd = nullptr;
+    // 1-D and 2-D grids (rkl_flat.h): their tilings, and three more fields of
+    // the largest one that is cut into several regions
+    std::vector<FlatTiling> flat, flat_once;
+    double* Fc = nullptr;       // the second pair of stage buffers
+    double* Fd = nullptr;
+    double* Fz = nullptr;       // copy of Y0
     void* MY0 = nullptr;        // tau M(Y0), FP64 or FP32, packed
     double* coef = nullptr;     // RKL2 table, device
     GridState* state = nullptr; // ngrids entries, device
@@ -180,6 +187,9 @@ static void free_plan(rkl_plan_s* p) {
     (void)hipFree(p->Yb);
     (void)hipFree(p->Yc);
     (void)hipFree(p->Yd);
+    (void)hipFree(p->Fc);
+    (void)hipFree(p->Fd);
+    (void)hipFree(p->Fz);
     (void)hipFree(p->MY0);
     (void)hipFree(p->coef);
     (void)hipFree(p->state);
@@ -403,6 +413,33 @@ static rkl_status select_variant(rkl_plan_s* p, int v) {
     return RKL_OK;
 }
 
+// Tilings of the plan's 1-D and 2-D grids and the scratch of the several-stage
+// launches; where it cannot be allocated those grids run one stage a launch.
+static void make_flat(rkl_plan_s* p) {
+    p->flat.resize(p->ngrids);
+    p->flat_once.resize(p->ngrids);
+    int64_t most = 0;
+    for (int g = 0; g < p->ngrids; ++g) {
+        const int64_t n = p->off[g + 1] - p->off[g];
+        if (p->gc[g].ndim > 2 || n > kFlatMostCells) continue;
+        p->flat[g] = flat_tiling(p->precision, p->gc[g]);
+        p->flat_once[g] = flat_tiling_once(p->precision, p->gc[g]);
+        if (p->flat[g].f && p->flat[g].blocks() > 1) most = std::max(most, n);
+    }
+    if (!most) return;
+    if (hipMalloc(&p->Fc, sizeof(double) * most) == hipSuccess &&
+        hipMalloc(&p->Fd, sizeof(double) * most) == hipSuccess &&
+        hipMalloc(&p->Fz, sizeof(double) * most) == hipSuccess)
+        return;
+    (void)hipGetLastError();
+    for (double** q : {&p->Fc, &p->Fd, &p->Fz}) {
+        (void)hipFree(*q);
+        *q = nullptr;
+    }
+    for (auto& t : p->flat)
+        if (t.blocks() > 1) t = FlatTiling();
+}
+
 rkl_status rkl_plan(const rkl_grid_desc* grids, int32_t ngrids, const rkl_options* opt, rkl_plan_t* out) {
     if (!out) return fail(RKL_EINVAL, "plan_out is NULL");
     *out = nullptr;
@@ -459,6 +496,7 @@ rkl_status rkl_plan(const rkl_grid_desc* grids, int32_t ngrids, const rkl_option
         free_plan(p);
         return fail(RKL_ENOMEM, "device allocation failed");
     }
+    make_flat(p);
     e = hipMemcpy(p->coef, tab.data(), sizeof(double) * tab.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(p->state, 0, sizeof(GridState) * ngrids);
     if (e == hipSuccess) e = hipMemset(p->ext_ok, 0, sizeof(int32_t) * ngrids);
@@ -534,6 +572,68 @@ static Variant routed(rkl_plan_t p, int32_t g) {
     return fit_variant(p->precision, v.fuse == 1 ? v : variant_get(0), p->gc[g]);
 }
 
+// ------------------------------------------------- 1-D and 2-D grids ----
+// several stages per launch; while kernel timing records, one (the timing is
+// per stage launch)
+static bool use_flat(rkl_plan_t p, int32_t g) { return p->flat[g].f > 0 && !p->prof; }
+
+// what the launches of a 1-D or 2-D grid share; the state comes from T, on
+// larger grids from the reduction's partial extrema (launched here)
+static rkl_status flat_start(rkl_plan_t p, int32_t g, const FlatTiling& t, const double* T, const void* b,
+                             FlatLaunch* P, hipStream_t st) {
+    const int64_t N = p->off[g + 1] - p->off[g];
+    const size_t rs = p->precision == RKL_MIXED ? sizeof(float) : sizeof(double);
+    *P = FlatLaunch();
+    P->T = T;
+    P->Y0c = p->Fz;
+    P->M = (char*)p->MY0 + rs * p->off[g];
+    P->b = b;
+    P->state = p->state + g;
+    P->coef = p->coef;
+    P->t = t;
+    P->gc = p->gc[g];
+    P->smin = p->scheme == RKL_RKL1 ? 1 : 2;
+    P->s_cap = p->smax;
+    P->partials = p->partials;
+    if (N <= kFlatFieldCells) {
+        P->from = kFlatFromField;
+    } else {
+        P->from = kFlatFromPartials;
+        P->npart = std::min(reduce_blocks(N), 256);
+        HIPCHECK(launch_reduce(T, N, p->partials, P->npart, st), "reduce launch");
+    }
+    return RKL_OK;
+}
+
+// one group of a super-step; the pairs of stage buffers alternate
+static rkl_status flat_group(rkl_plan_t p, int32_t g, FlatLaunch& P, int group, hipStream_t st) {
+    double *A = p->Ya + p->off[g], *B = p->Yb + p->off[g];
+    P.kind = 1;
+    P.group = group;
+    if (group > 0) P.from = kFlatStateReady;
+    P.out1 = group % 2 == 0 ? A : p->Fc;
+    P.out2 = group % 2 == 0 ? B : p->Fd;
+    P.in1 = group % 2 == 0 ? p->Fc : A;
+    P.in2 = group % 2 == 0 ? p->Fd : B;
+    HIPCHECK(launch_flat(p->precision, P, st), "stage group launch");
+    return RKL_OK;
+}
+
+// a super-step with s on the device (at most s_cap)
+static rkl_status flat_superstep_async(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_hyp, int32_t s_cap,
+                                       int32_t* s_out, hipStream_t st) {
+    FlatLaunch P;
+    if (rkl_status e = flat_start(p, g, p->flat[g], T, b, &P, st)) return e;
+    P.Tout = T;
+    P.dt_hyp = dt_hyp;
+    P.s_cap = s_cap;
+    P.s_out = s_out;
+    P.groups = flat_groups(P.t, s_cap);
+    for (int k = 0; k < P.groups; ++k)
+        if (rkl_status e = flat_group(p, g, P, k, st)) return e;
+    return RKL_OK;
+}
+
 // min/max reduction of T and the finalize step for grid g
 static rkl_status reduce_and_finalize(rkl_plan_t p, int32_t g, const double* T, double dt_hyp, int mode,
                                       int32_t* s_dev, hipStream_t st, int smax = 0) {
@@ -552,6 +652,16 @@ rkl_status rkl_flux_div(rkl_plan_t p, int32_t g, const double* T, const void* b,
     if (!T || !b || !out) return fail(RKL_EINVAL, "NULL field pointer");
     if (out == T || (const void*)out == b) return fail(RKL_EINVAL, "out must not alias T or b");
     hipStream_t s = (hipStream_t)stream;
+    if (p->flat_once[g].f && !p->prof) {
+        FlatLaunch P;
+        if ((st = flat_start(p, g, p->flat_once[g], T, b, &P, s)) != RKL_OK) return st;
+        P.kind = 0;
+        P.first = 1;
+        P.Tout = out;
+        P.mode = 1;
+        HIPCHECK(launch_flat(p->precision, P, s), "flux_div launch");
+        return RKL_OK;
+    }
     st = reduce_and_finalize(p, g, T, 0.0, 1, nullptr, s);
     if (st != RKL_OK) return st;
     HIPCHECK(launch_stage(p->precision, fitted(p, g), p->gc[g], 0, 0, T, nullptr, nullptr, nullptr, nullptr,
@@ -583,7 +693,17 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
     if ((const void*)T == b) return fail(RKL_EINVAL, "b must not alias T");
     if (!(dt_hyp >= 0.0) || !std::isfinite(dt_hyp)) return fail(RKL_EINVAL, "dt_hyp must be finite and >= 0");
     hipStream_t s = (hipStream_t)stream;
-    st = reduce_and_finalize(p, g, T, dt_hyp, 0, p->s_dev, s);
+    FlatLaunch P;
+    if (use_flat(p, g)) {
+        // group 0 takes its share of the stages from the s it finds
+        if ((st = flat_start(p, g, p->flat[g], T, b, &P, s)) != RKL_OK) return st;
+        P.Tout = T;
+        P.dt_hyp = dt_hyp;
+        P.s_out = p->s_dev;
+        st = flat_group(p, g, P, 0, s);
+    } else {
+        st = reduce_and_finalize(p, g, T, dt_hyp, 0, p->s_dev, s);
+    }
     if (st != RKL_OK) return st;
     HIPCHECK(hipMemcpyAsync(p->s_host, p->s_dev, sizeof(int32_t), hipMemcpyDeviceToHost, s), "s copy");
     HIPCHECK(hipStreamSynchronize(s), "s sync");
@@ -593,6 +713,12 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
     if (S < smin || S > p->smax)
         return fail(RKL_ESTAGES, "stage count " + std::to_string(S) + " outside [" + std::to_string(smin) +
                                      ", smax=" + std::to_string(p->smax) + "]");
+    if (use_flat(p, g)) {
+        P.groups = flat_groups(P.t, S);
+        for (int k = 1; k < P.groups; ++k)
+            if ((st = flat_group(p, g, P, k, s)) != RKL_OK) return st;
+        return RKL_OK;
+    }
 
     const GridConst& gc = p->gc[g];
     const Variant v = variant_get(p->variant), v1 = fitted(p, g);
@@ -672,6 +798,7 @@ rkl_status rkl_superstep_async(rkl_plan_t p, int32_t g, double* T, const void* b
     if (s_cap < 2 || s_cap > p->smax)
         return fail(RKL_EINVAL, "s_cap must be in [2, smax=" + std::to_string(p->smax) + "]");
     hipStream_t s = (hipStream_t)stream;
+    if (use_flat(p, g)) return flat_superstep_async(p, g, T, b, dt_hyp, s_cap, s_out, s);
     // s on the device; stages beyond it (and every stage, if s > s_cap) return at once
     st = reduce_and_finalize(p, g, T, dt_hyp, 0, s_out, s, s_cap);
     if (st != RKL_OK) return st;
@@ -700,6 +827,12 @@ rkl_status rkl_supersteps_async(rkl_plan_t p, int32_t g, double* T, const void* 
         return fail(RKL_EINVAL, "s_cap must be in [2, smax=" + std::to_string(p->smax) + "]");
     if (nsteps < 1) return fail(RKL_EINVAL, "nsteps must be >= 1");
     hipStream_t s = (hipStream_t)stream;
+    if (use_flat(p, g)) {
+        for (int32_t i = 0; i < nsteps; ++i)
+            if ((st = flat_superstep_async(p, g, T, b, dt_hyp, s_cap, s_out ? s_out + i : nullptr, s)) != RKL_OK)
+                return st;
+        return RKL_OK;
+    }
     const GridConst& gc = p->gc[g];
     const Variant v = routed(p, g);
     // the compile-time-shaped stage kernels keep the last stage's extrema;
@@ -738,6 +871,34 @@ static rkl_status euler_substeps(rkl_plan_t p, int32_t g, double* T, const void*
     const Variant v = fitted(p, g);
     const int64_t n = p->off[g + 1] - p->off[g];
     double* A = p->Ya + p->off[g];
+    if (use_flat(p, g)) {
+        // launches of up to f sub-steps; with several regions the first does
+        // not write T and the last does not read it
+        FlatLaunch P;
+        P = FlatLaunch();
+        P.kind = 2;
+        P.T = T;
+        P.Tout = T;
+        P.b = b;
+        P.state = p->state + g;
+        P.t = p->flat[g];
+        P.gc = gc;
+        const bool one = P.t.blocks() == 1;
+        const int64_t f = std::min(P.t.f, kFlatEuler);
+        int64_t groups = (count + f - 1) / f;
+        if (!one && groups < 2) groups = 2;
+        for (int64_t k = 0; k < groups; ++k) {
+            const int64_t c0 = count * k / groups, c1 = count * (k + 1) / groups;
+            P.first = one || k == 0;
+            P.last = one || k == groups - 1;
+            P.count = (int)(c1 - c0);
+            for (int64_t i = c0; i < c1; ++i) P.scale[i - c0] = -tau(i) * gc.fac;
+            P.out1 = k % 2 == 0 ? A : p->Fc;
+            P.in1 = k % 2 == 0 ? p->Fc : A;
+            HIPCHECK(launch_flat(p->precision, P, s), "sub-step launch");
+        }
+        return RKL_OK;
+    }
     for (int64_t k = 0; k < count; ++k) {
         const double* in = (k % 2 == 0) ? T : A;
         double* out = (k % 2 == 0) ? A : T;

@@ -1,0 +1,92 @@
+// rkl_flat.h -- several stages per launch on 1-D and 2-D grids (gfx950).
+// Private to librkl.
+//
+// Method: Vaidya et al. (2017), arXiv:1702.05487, Appendix A (RKL2, and RKL1
+// of Sec. 3.3) and the explicit sub-steps of Sec. 2.3, with the face flux of
+// rkl_tile.h.
+//
+// What bounds it: a 1-D or 2-D stage of these grids is a few hundred
+// nanoseconds of arithmetic, so one launch per stage spends its time on the
+// launch itself (2.6 us for an empty one) and on filling the pipeline.  Here
+// a workgroup holds a region of the grid, one cell per thread, for F stages:
+// the stage values of the cell stay in registers, the input and its slopes in
+// LDS, and the field directions of its faces are formed once.  A region
+// reaches F cells beyond its output tile (each stage needs one cell around
+// it, including the corners), except at edges the region itself knows: an
+// outflow or fixed edge, or a periodic axis that lies in the region whole.
+// The cells of the border are computed by the neighbouring workgroups too.
+//
+// A super-step of s stages is cut into G groups of at most F stages, one
+// launch each.  Group 0 reads T, takes dt_par, s and T_ref (from T itself or
+// from the reduction's partial extrema, each workgroup for itself) and keeps
+// tau M(Y0) and a copy of Y0; each group hands Y_j and Y_{j-1} on in a pair of
+// buffers that it does not read; the last writes T, which no workgroup of its
+// launch reads.  So G >= 2, unless one workgroup holds the whole grid.
+// Every operation is that of run_tile, so the results have its bits.
+#pragma once
+#include "rkl_internal.h"
+
+namespace rkl {
+
+constexpr int kFlatThreads = 1024;   // most threads (and cells) of a workgroup
+constexpr int kFlatEuler = 64;       // most sub-steps of one Euler launch
+constexpr int64_t kFlatMostCells = int64_t(1) << 26;   // larger grids run one stage a launch
+
+// How a 1-D or 2-D grid is cut: regions of at most w x h cells, output tiles
+// of o0 x o1 cells, at most f stages a launch.
+struct FlatTiling {
+    int w = 0, h = 0, o0 = 0, o1 = 0, nt0 = 0, nt1 = 0, f = 0;
+    int threads = 0;
+    int blocks() const { return nt0 * nt1; }
+};
+// the tiling for grid gc (1-D or 2-D), or f = 0 where one launch per stage is used
+FlatTiling flat_tiling(int precision, const GridConst& gc);
+// the tiling of a single operator evaluation
+FlatTiling flat_tiling_once(int precision, const GridConst& gc);
+// groups of a super-step of s stages
+inline int flat_groups(const FlatTiling& t, int s) {
+    if (t.blocks() == 1) return 1;
+    const int g = (s + t.f - 1) / t.f;
+    return g < 2 ? 2 : g;
+}
+
+// where group 0 takes the state from: nothing (already in *state), the field
+// itself (small grids: every workgroup reads it), or partial extrema
+enum { kFlatStateReady = 0, kFlatFromField = 1, kFlatFromPartials = 2 };
+constexpr int64_t kFlatFieldCells = 16384;   // most cells that every workgroup reads for itself
+
+struct FlatLaunch {
+    int kind;            // 0 flux divergence, 1 super-step group, 2 Euler sub-steps
+    const double* T;     // Y0: the stencil input of group 0
+    double* Tout;        // kind 0: out; else T, written by the last group
+    double* Y0c;         // copy of Y0, written by group 0
+    void* M;             // tau M(Y0), type R
+    const double* in1;   // groups >= 1: Y_{j0-1}
+    const double* in2;   //              Y_{j0-2}
+    double* out1;        // groups before the last: Y_{j1}
+    double* out2;        //                         Y_{j1-1}
+    const void* b;
+    GridState* state;
+    const double* coef;  // RKL table, row (s, j) at 5 (s(s+1)/2 + j); NULL: RKL2 rows formed here
+    int group, groups;   // groups 0: as many as flat_groups gives for s
+    int smin, s_cap;     // s outside [smin, s_cap]: nothing is done
+    FlatTiling t;
+    GridConst gc;
+    int from;            // kFlat...
+    const double* partials;
+    int npart;
+    double dt_hyp;
+    int mode;            // finalize_state's
+    int32_t* s_out;      // device, may be NULL
+    int first, last;     // kind 2: the first reads T, the last writes Tout
+    int count;           // kind 2: sub-steps of this launch
+    double scale[kFlatEuler];   // kind 2: -tau_k (gamma-1)/rho
+};
+
+hipError_t launch_flat(int precision, const FlatLaunch& P, hipStream_t st);
+template <typename R>
+hipError_t launch_flat_r(const FlatLaunch& P, hipStream_t st);
+extern template hipError_t launch_flat_r<float>(const FlatLaunch&, hipStream_t);
+extern template hipError_t launch_flat_r<double>(const FlatLaunch&, hipStream_t);
+
+}  // namespace rkl

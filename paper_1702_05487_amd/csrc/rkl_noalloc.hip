@@ -12,11 +12,13 @@
 // is used.  Every call on one GPU shares that GPU's array; calls that
 // overlap on one GPU race.  Nothing in the array needs to start at zero:
 // each call writes every part before it reads it.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <string>
 
 #include "../../include/rkl.h"
+#include "rkl_flat.h"
 #include "rkl_host.h"
 #include "rkl_internal.h"
 
@@ -96,6 +98,46 @@ extern "C" rkl_status rkl_superstep_noalloc(const rkl_grid_desc* grid, int32_t p
 
     hipStream_t s = (hipStream_t)stream;
     const GridConst gc = make_const(*grid, RKL_RKL2);
+    // 1-D and 2-D grids: several stages per launch (rkl_flat.h), where the
+    // array holds the three further fields of a grid cut into several regions
+    const FlatTiling ft = grid->ndim <= 2 ? flat_tiling(precision, gc) : FlatTiling();
+    if (ft.f && (ft.blocks() == 1 || 2 * N <= kCells)) {
+        FlatLaunch P = FlatLaunch();
+        double* f = (double*)base;   // five fields, then tau M(Y0)
+        P.kind = 1;
+        P.T = T;
+        P.Tout = T;
+        P.Y0c = f + 4 * N;
+        P.M = f + 5 * N;
+        P.b = b;
+        P.state = state;
+        P.groups = flat_groups(ft, s_cap);
+        P.smin = 2;
+        P.s_cap = s_cap;
+        P.t = ft;
+        P.gc = gc;
+        P.dt_hyp = dt_hyp;
+        P.s_out = s_out;
+        P.partials = part;
+        P.npart = std::min(reduce_blocks(N), 256);
+        P.from = N <= kFlatFieldCells ? kFlatFromField : kFlatFromPartials;
+        if (P.from == kFlatFromPartials) {
+            const hipError_t re = launch_reduce(T, N, part, P.npart, s);
+            if (re != hipSuccess) return hipfail(re, "reduce launch");
+        }
+        for (int k = 0; k < P.groups; ++k) {
+            P.group = k;
+            if (k > 0) P.from = kFlatStateReady;
+            const int o = k % 2 == 0 ? 0 : 2, i = 2 - o;
+            P.out1 = f + o * N;
+            P.out2 = f + (o + 1) * N;
+            P.in1 = f + i * N;
+            P.in2 = f + (i + 1) * N;
+            const hipError_t le = launch_flat(precision, P, s);
+            if (le != hipSuccess) return hipfail(le, "stage group launch");
+        }
+        return RKL_OK;
+    }
     const int nb = reduce_blocks(N);
     hipError_t e = launch_reduce(T, N, part, nb, s);
     if (e != hipSuccess) return hipfail(e, "reduce launch");

@@ -130,6 +130,26 @@ __device__ __forceinline__ FaceK<R> make_facek(double kappa0, double kexp, doubl
     return k;
 }
 
+// The field direction at a face: c = b_L + b_R along the face normal and the
+// two transverse axes, and 1/|c|^2.
+template <typename R>
+struct FaceDir {
+    R cn, c1, c2, rc;
+    bool ok;             // |c| >= 1e-12
+};
+
+template <typename R>
+__device__ __forceinline__ FaceDir<R> face_dir(R bLn, R bL1, R bL2, R bRn, R bR1, R bR2) {
+    FaceDir<R> d;
+    d.cn = bLn + bRn;
+    d.c1 = bL1 + bR1;
+    d.c2 = bL2 + bR2;
+    const R cc = fma(d.cn, d.cn, fma(d.c1, d.c1, d.c2 * d.c2));
+    d.ok = !(cc < R(1e-24));
+    d.rc = r_rcp(cc);
+    return d;
+}
+
 // Normal component of F_c through a face, for cells L (low) and R (high)
 // along the face normal.  SAT: 0 classical flux, 1 saturated blend with q at
 // the face temperature, 2 the same with q at the temperature of the upwind
@@ -149,21 +169,18 @@ __device__ __forceinline__ FaceK<R> make_facek(double kappa0, double kexp, doubl
 // saturated flux 5 phi rho T^1.5 as satq T^2/sqrt(T) with the same T^1.5
 // (one reciprocal root; T is clipped at 1e-30 instead of 0 so that the root
 // stays finite, which changes kappa and q by less than 1e-75).
-template <typename R, bool LIM, int SAT, int KM>
-__device__ __forceinline__ R face_flux(R TL, R TR, R ihn, R sL1, R sR1, R sL2, R sR2,
-                                       R bLn, R bL1, R bL2, R bRn, R bR1, R bR2,
-                                       const FaceK<R>& k) {
+//
+// face_flux_dir takes the transverse gradients and the direction; face_flux
+// forms them from the cells' slopes and unit vectors.
+template <typename R, int SAT, int KM>
+__device__ __forceinline__ R face_flux_dir(R TL, R TR, R ihn, R G1, R G2, const FaceDir<R>& d, const FaceK<R>& k) {
     const R Gn = (TR - TL) * ihn;
-    const R G1 = face_transverse<R, LIM>(sL1, sR1);
-    const R G2 = face_transverse<R, LIM>(sL2, sR2);
     const R Tf = fmax(fma(R(0.5), TL + TR, k.tref), R(1e-30));
     const R t15 = (SAT == 1 || KM == 1) ? (Tf * Tf) * r_rsqrt(Tf) : R(0);   // T^1.5
     const R kpar = KM == 0 ? k.kappa0 : (KM == 1 ? k.kappa0 * (t15 * Tf) : k.kappa0 * r_pow(Tf, k.kexp));
-    const R cn = bLn + bRn, c1 = bL1 + bR1, c2 = bL2 + bR2;
-    const R cc = fma(cn, cn, fma(c1, c1, c2 * c2));
-    const R cG = fma(cn, Gn, fma(c1, G1, c2 * G2));
-    const R w = cc < R(1e-24) ? R(0) : cG * r_rcp(cc);     // (b.G)/|c|
-    const R A = fma(k.r, Gn, k.omr * (cn * w));
+    const R cG = fma(d.cn, Gn, fma(d.c1, G1, d.c2 * G2));
+    const R w = d.ok ? cG * d.rc : R(0);                   // (b.G)/|c|
+    const R A = fma(k.r, Gn, k.omr * (d.cn * w));
     if (SAT == 0) return -(kpar * A);
     const R GG = fma(Gn, Gn, fma(G1, G1, G2 * G2));
     const R B2 = fma(k.r2, GG, k.omr2 * (cG * w));
@@ -176,6 +193,15 @@ __device__ __forceinline__ R face_flux(R TL, R TR, R ihn, R sL1, R sR1, R sL2, R
     }
     const R den = fma(kpar, r_sqrt(B2), q);    // q + |F|; B2 >= 0: sums of products of non-negative terms
     return den > R(0) ? -(kpar * A) * (q * r_rcp(den)) : R(0);
+}
+
+template <typename R, bool LIM, int SAT, int KM>
+__device__ __forceinline__ R face_flux(R TL, R TR, R ihn, R sL1, R sR1, R sL2, R sR2,
+                                       R bLn, R bL1, R bL2, R bRn, R bR1, R bR2,
+                                       const FaceK<R>& k) {
+    const FaceDir<R> d = face_dir(bLn, bL1, bL2, bRn, bR1, bR2);
+    return face_flux_dir<R, SAT, KM>(TL, TR, ihn, face_transverse<R, LIM>(sL1, sR1),
+                                     face_transverse<R, LIM>(sL2, sR2), d, k);
 }
 
 // ------------------------------------------------------------- one tile ----
