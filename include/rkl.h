@@ -32,7 +32,7 @@
  *   - The caller owns every pointer it passes; the plan owns its scratch.
  *   - `stream` is a hipStream_t (NULL = the legacy default stream).  Work is
  *     enqueued on it; entry points that must read a device result back say
- *     so and synchronise that stream.
+ *     so and wait for it on the host.
  *   - Every entry point returns an rkl_status; nothing aborts and no C++
  *     exception crosses the ABI.  rkl_last_error() gives a message for the
  *     calling thread's last non-OK status.
@@ -184,8 +184,9 @@ rkl_status rkl_flux_div(rkl_plan_t plan, int32_t grid, const double *T, const vo
 /*
  * rkl_dt_par: the explicit parabolic step of Eq. dt_exp with the HD
  * diffusivity, dt_par = cp / max_i[(gamma-1)/rho * kappa_par(T_i) * sum_d h_d^-2]
- * (+inf when the maximum is 0).  Writes the host double *dt_par_out and
- * synchronises `stream`.
+ * (+inf when the maximum is 0).  Writes the host double *dt_par_out once the
+ * value is there (what was enqueued on `stream` before the call has then
+ * finished).
  */
 rkl_status rkl_dt_par(rkl_plan_t plan, int32_t grid, const double *T, double *dt_par_out,
                       void *stream);
@@ -197,8 +198,9 @@ rkl_status rkl_dt_par(rkl_plan_t plan, int32_t grid, const double *T, double *dt
  * + gt_j tau M(Y0), T = Y_s), where M is the flux-divergence operator above
  * evaluated on each stage's own temperature.  s = 1 + floor(root of
  * dt_hyp/dt_par = (s^2+s-2)/4) is computed on the device (Eq. RKL-s); this
- * entry point reads it back once (one synchronisation of `stream`) to size
- * the launch sequence, and stores it in *s_out (host pointer, may be NULL).
+ * entry point waits on the host for s alone (the first stages are already
+ * enqueued and run meanwhile) to size the launch sequence, and stores it in
+ * *s_out (host pointer, may be NULL).
  * RKL_ESTAGES (T unchanged) if s > smax.  b must not alias T (RKL_EINVAL;
  * likewise for the other entry points that take T and b).
  * With scheme RKL_RKL1 the super-step is the first-order scheme: stability
@@ -277,7 +279,7 @@ rkl_status rkl_superstep_noalloc(const rkl_grid_desc *grid, int32_t precision, d
  * paper compares super-time-stepping with): N_sub = ceil(dt_hyp / dt_par)
  * forward-Euler sub-steps T <- T + tau (gamma-1)/rho (-div F_c(T)) with
  * tau = dt_hyp / N_sub <= dt_par, dt_par of Eq. dt_exp taken from T at the
- * start.  Reads dt_par back once (one synchronisation of `stream`); stores
+ * start.  Waits on the host for dt_par once, as rkl_dt_par does; stores
  * N_sub in *nsub_out (host pointer, may be NULL; 0 when dt_hyp = 0 or there
  * is no conduction, T then unchanged).  RKL_ESTAGES (T unchanged) if N_sub
  * would exceed max_sub.  Uses one plan stage buffer as the other half of a
@@ -293,7 +295,7 @@ rkl_status rkl_subcycle(rkl_plan_t plan, int32_t grid, double *T, const void *b,
  * damped Chebyshev sequence tau_j = dt_par / ((nu-1) cos(pi (2j-1)/(2S)) +
  * 1 + nu), j = 1..S, scaled to sum to dt_hyp, where S is the smallest count
  * whose gain (Eq. AAG-STS) reaches dt_hyp/dt_par.  nu in (0, 1) is the
- * damping.  Reads dt_par back once (one synchronisation); *s_out (host, may
+ * damping.  Waits on the host for dt_par once; *s_out (host, may
  * be NULL) receives S (0: nothing to do).  RKL_ESTAGES (T unchanged) if S
  * would exceed max_s.  Same kernels and ping-pong as rkl_subcycle.
  */

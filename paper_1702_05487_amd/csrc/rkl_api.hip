@@ -49,17 +49,17 @@ struct rkl_plan_s {
     // 1-D and 2-D grids (rkl_flat.h): their tilings, and three more fields of
     // the largest one that is cut into several regions
     std::vector<FlatTiling> flat, flat_once;
-    double* Fc = nullptr;       // the second pair of stage buffers
+    double* Fc = nullptr;       // the second pair of stage buffers (one allocation with Fd and Fz)
     double* Fd = nullptr;
     double* Fz = nullptr;       // copy of Y0
     void* MY0 = nullptr;        // tau M(Y0), FP64 or FP32, packed
     double* coef = nullptr;     // RKL2 table, device
-    GridState* state = nullptr; // ngrids entries, device
+    char* small = nullptr;      // device, one allocation of the next four:
+    GridState* state = nullptr; // ngrids entries
+    int32_t* ext_ok = nullptr;  // ngrids flags: ext_part holds the extrema of the grid's T
     double* partials = nullptr; // 3 x 1024 doubles
     double* ext_part = nullptr; // 3 per workgroup of a one-stage launch, the largest over grids and variants
-    int32_t* ext_ok = nullptr;  // ngrids flags: ext_part holds the extrema of the grid's T
-    int32_t* s_dev = nullptr;   // scratch for the stage-count read-back
-    int32_t* s_host = nullptr;  // pinned
+    HostWords* host = nullptr;  // pinned: dt_par and s for the calls that return them
     BatchPlan* batch = nullptr; // batched launch data (rkl_batch.hip)
     int batch_policy = 0;       // its tile policy
     int batch_mode = 0;         // 0: one launch per stage; 1: one persistent launch
@@ -188,16 +188,10 @@ static void free_plan(rkl_plan_s* p) {
     (void)hipFree(p->Yc);
     (void)hipFree(p->Yd);
     (void)hipFree(p->Fc);
-    (void)hipFree(p->Fd);
-    (void)hipFree(p->Fz);
     (void)hipFree(p->MY0);
     (void)hipFree(p->coef);
-    (void)hipFree(p->state);
-    (void)hipFree(p->partials);
-    (void)hipFree(p->ext_part);
-    (void)hipFree(p->ext_ok);
-    (void)hipFree(p->s_dev);
-    if (p->s_host) (void)hipHostFree(p->s_host);
+    (void)hipFree(p->small);
+    if (p->host) (void)hipHostFree(p->host);
     delete p;
 }
 
@@ -427,15 +421,13 @@ static void make_flat(rkl_plan_s* p) {
         if (p->flat[g].f && p->flat[g].blocks() > 1) most = std::max(most, n);
     }
     if (!most) return;
-    if (hipMalloc(&p->Fc, sizeof(double) * most) == hipSuccess &&
-        hipMalloc(&p->Fd, sizeof(double) * most) == hipSuccess &&
-        hipMalloc(&p->Fz, sizeof(double) * most) == hipSuccess)
+    if (hipMalloc(&p->Fc, sizeof(double) * 3 * most) == hipSuccess) {
+        p->Fd = p->Fc + most;
+        p->Fz = p->Fd + most;
         return;
-    (void)hipGetLastError();
-    for (double** q : {&p->Fc, &p->Fd, &p->Fz}) {
-        (void)hipFree(*q);
-        *q = nullptr;
     }
+    (void)hipGetLastError();
+    p->Fc = nullptr;
     for (auto& t : p->flat)
         if (t.blocks() > 1) t = FlatTiling();
 }
@@ -481,25 +473,27 @@ rkl_status rkl_plan(const rkl_grid_desc* grids, int32_t ngrids, const rkl_option
         for (int v = 0; v < variant_count(); ++v)
             if (variant_get(v).fuse == 1)
                 ext_blocks = std::max(ext_blocks, stage_blocks(fit_variant(p->precision, variant_get(v), p->gc[g]), p->gc[g]));
+    const auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+    const size_t b_ok = up(sizeof(GridState) * ngrids), b_part = b_ok + up(sizeof(int32_t) * ngrids),
+                 b_ext = b_part + up(sizeof(double) * 3 * 1024);
     bool ok = hipMalloc(&p->Ya, sizeof(double) * p->total) == hipSuccess &&
               hipMalloc(&p->Yb, sizeof(double) * p->total) == hipSuccess &&
               hipMalloc(&p->MY0, rs * p->total) == hipSuccess &&
               hipMalloc(&p->coef, sizeof(double) * tab.size()) == hipSuccess &&
-              hipMalloc(&p->state, sizeof(GridState) * ngrids) == hipSuccess &&
-              hipMalloc(&p->partials, sizeof(double) * 3 * 1024) == hipSuccess &&
-              hipMalloc(&p->ext_part, sizeof(double) * 3 * ext_blocks) == hipSuccess &&
-              hipMalloc(&p->ext_ok, sizeof(int32_t) * ngrids) == hipSuccess &&
-              hipMalloc(&p->s_dev, sizeof(int32_t)) == hipSuccess &&
-              hipHostMalloc((void**)&p->s_host, sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
+              hipMalloc(&p->small, b_ext + sizeof(double) * 3 * ext_blocks) == hipSuccess &&
+              hipHostMalloc((void**)&p->host, sizeof(HostWords), hipHostMallocDefault) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         free_plan(p);
         return fail(RKL_ENOMEM, "device allocation failed");
     }
+    p->state = (GridState*)p->small;
+    p->ext_ok = (int32_t*)(p->small + b_ok);
+    p->partials = (double*)(p->small + b_part);
+    p->ext_part = (double*)(p->small + b_ext);
     make_flat(p);
     e = hipMemcpy(p->coef, tab.data(), sizeof(double) * tab.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(p->state, 0, sizeof(GridState) * ngrids);
-    if (e == hipSuccess) e = hipMemset(p->ext_ok, 0, sizeof(int32_t) * ngrids);
+    if (e == hipSuccess) e = hipMemset(p->small, 0, b_part);
     // the set-up above is ordered on the legacy stream; finish it so that the
     // caller's first launch on any stream sees it
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -572,16 +566,69 @@ static Variant routed(rkl_plan_t p, int32_t g) {
     return fit_variant(p->precision, v.fuse == 1 ? v : variant_get(0), p->gc[g]);
 }
 
+// the extrema of T as the source of a state for workgroups of `threads`: T
+// itself where each reads it quickly, else the partial extrema of a reduction,
+// at most `most_parts` (launched here; `skip` as in launch_reduce)
+static rkl_status extrema_source(rkl_plan_t p, int32_t g, const double* T, double dt_hyp, int mode, int smax,
+                                 int threads, int most_parts, StateSource* q, hipStream_t st,
+                                 const int32_t* skip = nullptr) {
+    const int64_t N = p->off[g + 1] - p->off[g];
+    if (N <= kFieldCells * threads && !skip) {
+        *q = partials_source(nullptr, 0, dt_hyp, mode, smax, nullptr);
+        q->field = T;
+        q->field_n = N;
+        return RKL_OK;
+    }
+    const int nb = std::min(reduce_blocks(N), most_parts);
+    HIPCHECK(launch_reduce(T, N, p->partials, nb, st, skip), "reduce launch");
+    *q = partials_source(p->partials, nb, dt_hyp, mode, smax, nullptr);
+    return RKL_OK;
+}
+
+// Read-back of dt_par and s.  arm_host before the launch that stores them,
+// wait_host after everything that may run meanwhile has been enqueued: it
+// polls the pinned words (the stream is not drained), looking at the stream
+// now and then so that a failed launch ends the wait.  Waits for both words,
+// so that no store is left for a later call.
+static rkl_status arm_host(rkl_plan_t p, hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    HIPCHECK(hipStreamIsCapturing(st, &cs), "capture query");
+    if (cs != hipStreamCaptureStatusNone) return hipfail(hipErrorStreamCaptureUnsupported, "read-back");
+    __atomic_store_n(&p->host->s, kNoStages, __ATOMIC_RELAXED);
+    double none = kNoDtPar;
+    __atomic_store(&p->host->dt_par, &none, __ATOMIC_SEQ_CST);
+    return RKL_OK;
+}
+
+static rkl_status wait_host(rkl_plan_t p, hipStream_t st, HostWords* out) {
+    const auto there = [&] {
+        out->s = __atomic_load_n(&p->host->s, __ATOMIC_ACQUIRE);
+        __atomic_load(&p->host->dt_par, &out->dt_par, __ATOMIC_ACQUIRE);
+        return out->s != kNoStages && out->dt_par != kNoDtPar;
+    };
+    for (int64_t spin = 1;; ++spin) {
+        if (there()) return RKL_OK;
+        if (spin % 4096) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipErrorNotReady) continue;
+        if (e != hipSuccess) return hipfail(e, "read-back");
+        if (there()) return RKL_OK;   // the stream has drained
+        return fail(RKL_EDEVICE, "read-back: the launch stored no result");
+    }
+}
+
 // ------------------------------------------------- 1-D and 2-D grids ----
 // several stages per launch; while kernel timing records, one (the timing is
 // per stage launch)
 static bool use_flat(rkl_plan_t p, int32_t g) { return p->flat[g].f > 0 && !p->prof; }
 
-// what the launches of a 1-D or 2-D grid share; the state comes from T, on
-// larger grids from the reduction's partial extrema (launched here)
+// what the launches of a 1-D or 2-D grid share; every workgroup of the first
+// one forms the state
 static rkl_status flat_start(rkl_plan_t p, int32_t g, const FlatTiling& t, const double* T, const void* b,
-                             FlatLaunch* P, hipStream_t st) {
-    const int64_t N = p->off[g + 1] - p->off[g];
+                             double dt_hyp, int mode, int s_cap, FlatLaunch* P, hipStream_t st) {
     const size_t rs = p->precision == RKL_MIXED ? sizeof(float) : sizeof(double);
     *P = FlatLaunch();
     P->T = T;
@@ -593,16 +640,9 @@ static rkl_status flat_start(rkl_plan_t p, int32_t g, const FlatTiling& t, const
     P->t = t;
     P->gc = p->gc[g];
     P->smin = p->scheme == RKL_RKL1 ? 1 : 2;
-    P->s_cap = p->smax;
-    P->partials = p->partials;
-    if (N <= kFlatFieldCells) {
-        P->from = kFlatFromField;
-    } else {
-        P->from = kFlatFromPartials;
-        P->npart = std::min(reduce_blocks(N), 256);
-        HIPCHECK(launch_reduce(T, N, p->partials, P->npart, st), "reduce launch");
-    }
-    return RKL_OK;
+    P->s_cap = s_cap;
+    P->derive = 1;
+    return extrema_source(p, g, T, dt_hyp, mode, s_cap, t.threads, 256, &P->src, st);
 }
 
 // one group of a super-step; the pairs of stage buffers alternate
@@ -610,7 +650,7 @@ static rkl_status flat_group(rkl_plan_t p, int32_t g, FlatLaunch& P, int group, 
     double *A = p->Ya + p->off[g], *B = p->Yb + p->off[g];
     P.kind = 1;
     P.group = group;
-    if (group > 0) P.from = kFlatStateReady;
+    if (group > 0) P.derive = 0;
     P.out1 = group % 2 == 0 ? A : p->Fc;
     P.out2 = group % 2 == 0 ? B : p->Fd;
     P.in1 = group % 2 == 0 ? p->Fc : A;
@@ -623,25 +663,12 @@ static rkl_status flat_group(rkl_plan_t p, int32_t g, FlatLaunch& P, int group, 
 static rkl_status flat_superstep_async(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_hyp, int32_t s_cap,
                                        int32_t* s_out, hipStream_t st) {
     FlatLaunch P;
-    if (rkl_status e = flat_start(p, g, p->flat[g], T, b, &P, st)) return e;
+    if (rkl_status e = flat_start(p, g, p->flat[g], T, b, dt_hyp, 0, s_cap, &P, st)) return e;
     P.Tout = T;
-    P.dt_hyp = dt_hyp;
-    P.s_cap = s_cap;
-    P.s_out = s_out;
+    P.src.s_out = s_out;
     P.groups = flat_groups(P.t, s_cap);
     for (int k = 0; k < P.groups; ++k)
         if (rkl_status e = flat_group(p, g, P, k, st)) return e;
-    return RKL_OK;
-}
-
-// min/max reduction of T and the finalize step for grid g
-static rkl_status reduce_and_finalize(rkl_plan_t p, int32_t g, const double* T, double dt_hyp, int mode,
-                                      int32_t* s_dev, hipStream_t st, int smax = 0) {
-    const int64_t N = p->off[g + 1] - p->off[g];
-    const int nb = reduce_blocks(N);
-    HIPCHECK(launch_reduce(T, N, p->partials, nb, st), "reduce launch");
-    HIPCHECK(launch_finalize(p->partials, nb, p->gc[g], dt_hyp, mode, p->state + g, s_dev, smax ? smax : p->smax, st),
-             "finalize launch");
     return RKL_OK;
 }
 
@@ -654,19 +681,34 @@ rkl_status rkl_flux_div(rkl_plan_t p, int32_t g, const double* T, const void* b,
     hipStream_t s = (hipStream_t)stream;
     if (p->flat_once[g].f && !p->prof) {
         FlatLaunch P;
-        if ((st = flat_start(p, g, p->flat_once[g], T, b, &P, s)) != RKL_OK) return st;
+        if ((st = flat_start(p, g, p->flat_once[g], T, b, 0.0, 1, p->smax, &P, s)) != RKL_OK) return st;
         P.kind = 0;
         P.first = 1;
         P.Tout = out;
-        P.mode = 1;
         HIPCHECK(launch_flat(p->precision, P, s), "flux_div launch");
         return RKL_OK;
     }
-    st = reduce_and_finalize(p, g, T, 0.0, 1, nullptr, s);
-    if (st != RKL_OK) return st;
-    HIPCHECK(launch_stage(p->precision, fitted(p, g), p->gc[g], 0, 0, T, nullptr, nullptr, nullptr, nullptr,
+    const Variant v = fitted(p, g);
+    StateSource q;
+    if ((st = extrema_source(p, g, T, 0.0, 1, p->smax, 1024, 1024, &q, s)) != RKL_OK) return st;
+    HIPCHECK(launch_finalize(p->gc[g], q, p->state + g, nullptr, s), "finalize launch");
+    HIPCHECK(launch_stage(p->precision, v, p->gc[g], 0, 0, T, nullptr, nullptr, nullptr, nullptr,
                           out, b, p->state + g, p->coef, s),
              "flux_div launch");
+    return RKL_OK;
+}
+
+// dt_par of grid g from T, read back
+static rkl_status read_dt_par(rkl_plan_t p, int32_t g, const double* T, double* dtp, hipStream_t s) {
+    rkl_status st = arm_host(p, s);
+    if (st != RKL_OK) return st;
+    StateSource q;
+    if ((st = extrema_source(p, g, T, 0.0, 1, p->smax, 1024, 1024, &q, s)) != RKL_OK) return st;
+    q.host = p->host;
+    HIPCHECK(launch_finalize(p->gc[g], q, p->state + g, nullptr, s), "finalize launch");
+    HostWords w;
+    if ((st = wait_host(p, s, &w)) != RKL_OK) return st;
+    *dtp = w.dt_par;
     return RKL_OK;
 }
 
@@ -674,14 +716,7 @@ rkl_status rkl_dt_par(rkl_plan_t p, int32_t g, const double* T, double* dt_par_o
     rkl_status st = check_grid(p, g);
     if (st != RKL_OK) return st;
     if (!T || !dt_par_out) return fail(RKL_EINVAL, "NULL pointer");
-    hipStream_t s = (hipStream_t)stream;
-    st = reduce_and_finalize(p, g, T, 0.0, 1, nullptr, s);
-    if (st != RKL_OK) return st;
-    double v = 0.0;
-    HIPCHECK(hipMemcpyAsync(&v, &p->state[g].dt_par, sizeof(double), hipMemcpyDeviceToHost, s), "dt_par copy");
-    HIPCHECK(hipStreamSynchronize(s), "dt_par sync");
-    *dt_par_out = v;
-    return RKL_OK;
+    return read_dt_par(p, g, T, dt_par_out, (hipStream_t)stream);
 }
 
 rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_hyp, int32_t* s_out,
@@ -693,23 +728,37 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
     if ((const void*)T == b) return fail(RKL_EINVAL, "b must not alias T");
     if (!(dt_hyp >= 0.0) || !std::isfinite(dt_hyp)) return fail(RKL_EINVAL, "dt_hyp must be finite and >= 0");
     hipStream_t s = (hipStream_t)stream;
+    if ((st = arm_host(p, s)) != RKL_OK) return st;
+    const GridConst& gc = p->gc[g];
+    const Variant v = variant_get(p->variant), v1 = fitted(p, g);
+    const size_t rs = p->precision == RKL_MIXED ? sizeof(float) : sizeof(double);
+    void* M = (char*)p->MY0 + rs * p->off[g];
+    GridState* gs = p->state + g;
+    const int smin = p->scheme == RKL_RKL1 ? 1 : 2;
+    // the first launches go out before s is known: they take it on the device
     FlatLaunch P;
     if (use_flat(p, g)) {
-        // group 0 takes its share of the stages from the s it finds
-        if ((st = flat_start(p, g, p->flat[g], T, b, &P, s)) != RKL_OK) return st;
+        // group 0 finds its share of the stages from s
+        if ((st = flat_start(p, g, p->flat[g], T, b, dt_hyp, 0, p->smax, &P, s)) != RKL_OK) return st;
         P.Tout = T;
-        P.dt_hyp = dt_hyp;
-        P.s_out = p->s_dev;
-        st = flat_group(p, g, P, 0, s);
+        P.src.host = p->host;
+        if ((st = flat_group(p, g, P, 0, s)) != RKL_OK) return st;
     } else {
-        st = reduce_and_finalize(p, g, T, dt_hyp, 0, p->s_dev, s);
+        // stage 1, and stage 2 unless it may be part of a fused launch or is timed
+        StateSource q;
+        if ((st = extrema_source(p, g, T, dt_hyp, 0, p->smax, 1024, 1024, &q, s)) != RKL_OK) return st;
+        q.host = p->host;
+        HIPCHECK(launch_finalize(gc, q, gs, nullptr, s), "finalize launch");
+        const Route r{p->Ya + p->off[g], p->Yb + p->off[g], smin, p->smax, 0};
+        for (int j = 1; j <= (v.fuse == 1 && !p->prof ? 2 : 1); ++j)
+            HIPCHECK(launch_stage(p->precision, v1, gc, j, j, nullptr, nullptr, nullptr, M, M, T, b, gs, p->coef, s, 0.0,
+                                  &r),
+                     "stage launch");
     }
-    if (st != RKL_OK) return st;
-    HIPCHECK(hipMemcpyAsync(p->s_host, p->s_dev, sizeof(int32_t), hipMemcpyDeviceToHost, s), "s copy");
-    HIPCHECK(hipStreamSynchronize(s), "s sync");
-    const int S = *p->s_host;
+    HostWords words;
+    if ((st = wait_host(p, s, &words)) != RKL_OK) return st;
+    const int S = words.s;
     if (s_out) *s_out = S;
-    const int smin = p->scheme == RKL_RKL1 ? 1 : 2;
     if (S < smin || S > p->smax)
         return fail(RKL_ESTAGES, "stage count " + std::to_string(S) + " outside [" + std::to_string(smin) +
                                      ", smax=" + std::to_string(p->smax) + "]");
@@ -720,17 +769,9 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
         return RKL_OK;
     }
 
-    const GridConst& gc = p->gc[g];
-    const Variant v = variant_get(p->variant), v1 = fitted(p, g);
     const int64_t n = p->off[g + 1] - p->off[g];
     double* bufs[4] = {p->Ya + p->off[g], p->Yb + p->off[g], p->Yc ? p->Yc + p->off[g] : nullptr,
                        p->Yd ? p->Yd + p->off[g] : nullptr};
-    const size_t rs = p->precision == RKL_MIXED ? sizeof(float) : sizeof(double);
-    void* M = (char*)p->MY0 + rs * p->off[g];
-    const GridState* gs = p->state + g;
-    // stage 1: Y1 = Y0 + mut_1 tau M(Y0), tau M(Y0) kept for the later stages
-    HIPCHECK(launch_stage(p->precision, v1, gc, 1, 1, T, nullptr, nullptr, nullptr, M, bufs[0], b, gs, p->coef, s),
-             "stage 1 launch");
     // a stage buffer holding neither Y_{j-1} nor Y_{j-2}
     auto pick = [&](const double* u, const double* w, const double* x) -> double* {
         for (double* c : bufs)
@@ -740,6 +781,11 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
     const double* ym1 = bufs[0];
     const double* ym2 = T;
     int j = 2;
+    if (v.fuse == 1 && !p->prof && S >= 2) {   // stage 2 is on its way
+        ym1 = S == 2 ? T : bufs[1];
+        ym2 = bufs[0];
+        j = 3;
+    }
     while (j <= S) {
         hipEvent_t e0 = nullptr, e1 = nullptr;
         size_t rec = 0;
@@ -800,13 +846,15 @@ rkl_status rkl_superstep_async(rkl_plan_t p, int32_t g, double* T, const void* b
     hipStream_t s = (hipStream_t)stream;
     if (use_flat(p, g)) return flat_superstep_async(p, g, T, b, dt_hyp, s_cap, s_out, s);
     // s on the device; stages beyond it (and every stage, if s > s_cap) return at once
-    st = reduce_and_finalize(p, g, T, dt_hyp, 0, s_out, s, s_cap);
-    if (st != RKL_OK) return st;
     const GridConst& gc = p->gc[g];
     const Variant v = routed(p, g);
+    StateSource q;
+    if ((st = extrema_source(p, g, T, dt_hyp, 0, s_cap, 1024, 1024, &q, s)) != RKL_OK) return st;
+    q.s_out = s_out;
+    HIPCHECK(launch_finalize(gc, q, p->state + g, nullptr, s), "finalize launch");
     const size_t rs = p->precision == RKL_MIXED ? sizeof(float) : sizeof(double);
     void* M = (char*)p->MY0 + rs * p->off[g];
-    const Route r{p->Ya + p->off[g], p->Yb + p->off[g], s_cap, 0};
+    const Route r{p->Ya + p->off[g], p->Yb + p->off[g], 2, s_cap, 0};
     for (int j = 1; j <= s_cap; ++j)
         HIPCHECK(launch_stage(p->precision, v, gc, j == 1 ? 1 : 2, j, nullptr, nullptr, nullptr, M, M, T, b,
                               p->state + g, p->coef, s, 0.0, &r),
@@ -838,22 +886,26 @@ rkl_status rkl_supersteps_async(rkl_plan_t p, int32_t g, double* T, const void* 
     // the compile-time-shaped stage kernels keep the last stage's extrema;
     // other grids take the reduction pass before every super-step
     const bool keep = gc.ndim == 3 && !gc.fixed;
-    const int64_t N = p->off[g + 1] - p->off[g];
-    const int nb = reduce_blocks(N);
     const int64_t nbx = stage_blocks(v, gc);
     const size_t rs = p->precision == RKL_MIXED ? sizeof(float) : sizeof(double);
     void* M = (char*)p->MY0 + rs * p->off[g];
-    const Route r{p->Ya + p->off[g], p->Yb + p->off[g], s_cap, 0};
+    const Route r{p->Ya + p->off[g], p->Yb + p->off[g], 2, s_cap, 0};
     const ExtOut ext{p->ext_part, p->ext_ok + g};
     for (int32_t i = 0; i < nsteps; ++i) {
-        // super-step 0 always reduces (and clears the flag); later ones skip the
-        // pass when the previous super-step's last stage left the extrema
+        // super-step 0 always reduces; later ones skip the pass when the
+        // previous super-step's last stage left the extrema
         const bool chain = keep && i > 0;
-        HIPCHECK(launch_reduce(T, N, p->partials, nb, s, chain ? p->ext_ok + g : nullptr), "reduce launch");
-        HIPCHECK(launch_finalize(p->partials, nb, gc, dt_hyp, 0, p->state + g, s_out ? s_out + i : nullptr, s_cap,
-                                 s, nullptr, chain ? p->ext_part : nullptr, chain ? (int)nbx : 0,
-                                 keep ? p->ext_ok + g : nullptr),
-                 "finalize launch");
+        StateSource q;
+        if ((st = extrema_source(p, g, T, dt_hyp, 0, s_cap, 1024, 1024, &q, s,
+                                 chain ? p->ext_ok + g : nullptr)) != RKL_OK)
+            return st;
+        q.s_out = s_out ? s_out + i : nullptr;
+        if (chain) {
+            q.ext_part = p->ext_part;
+            q.ext_n = (int)nbx;
+            q.ext_ok = p->ext_ok + g;
+        }
+        HIPCHECK(launch_finalize(gc, q, p->state + g, keep ? p->ext_ok + g : nullptr, s), "finalize launch");
         for (int j = 1; j <= s_cap; ++j)
             HIPCHECK(launch_stage(p->precision, v, gc, j == 1 ? 1 : 2, j, nullptr, nullptr, nullptr, M, M, T, b,
                                   p->state + g, p->coef, s, 0.0, &r, keep && j >= 2 ? &ext : nullptr),
@@ -928,15 +980,6 @@ static rkl_status euler_substeps(rkl_plan_t p, int32_t g, double* T, const void*
     return RKL_OK;
 }
 
-// dt_par of grid g from T (reduction + one read-back)
-static rkl_status read_dt_par(rkl_plan_t p, int32_t g, const double* T, double* dtp, hipStream_t s) {
-    rkl_status st = reduce_and_finalize(p, g, T, 0.0, 1, nullptr, s);
-    if (st != RKL_OK) return st;
-    HIPCHECK(hipMemcpyAsync(dtp, &p->state[g].dt_par, sizeof(double), hipMemcpyDeviceToHost, s), "dt_par copy");
-    HIPCHECK(hipStreamSynchronize(s), "dt_par sync");
-    return RKL_OK;
-}
-
 rkl_status rkl_subcycle(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_hyp, int64_t max_sub,
                         int64_t* nsub_out, void* stream) {
     rkl_status st = check_grid(p, g);
@@ -949,8 +992,7 @@ rkl_status rkl_subcycle(rkl_plan_t p, int32_t g, double* T, const void* b, doubl
     if (max_sub < 1) return fail(RKL_EINVAL, "max_sub must be >= 1");
     hipStream_t s = (hipStream_t)stream;
     double dtp = 0.0;
-    st = read_dt_par(p, g, T, &dtp, s);
-    if (st != RKL_OK) return st;
+    if ((st = read_dt_par(p, g, T, &dtp, s)) != RKL_OK) return st;
     if (dt_hyp == 0.0 || std::isinf(dtp)) return RKL_OK;   // nothing to do
     // N_sub = ceil(dt_hyp / dt_par) forward-Euler sub-steps of dt_hyp / N_sub
     const double q = std::ceil(dt_hyp / dtp);
@@ -987,8 +1029,7 @@ rkl_status rkl_aag(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_
     if (max_s < 1) return fail(RKL_EINVAL, "max_s must be >= 1");
     hipStream_t s = (hipStream_t)stream;
     double dtp = 0.0;
-    st = read_dt_par(p, g, T, &dtp, s);
-    if (st != RKL_OK) return st;
+    if ((st = read_dt_par(p, g, T, &dtp, s)) != RKL_OK) return st;
     if (dt_hyp == 0.0 || std::isinf(dtp)) return RKL_OK;
     const double r = dt_hyp / dtp;
     int S = -1;

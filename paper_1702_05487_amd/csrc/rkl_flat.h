@@ -50,11 +50,6 @@ inline int flat_groups(const FlatTiling& t, int s) {
     return g < 2 ? 2 : g;
 }
 
-// where group 0 takes the state from: nothing (already in *state), the field
-// itself (small grids: every workgroup reads it), or partial extrema
-enum { kFlatStateReady = 0, kFlatFromField = 1, kFlatFromPartials = 2 };
-constexpr int64_t kFlatFieldCells = 16384;   // most cells that every workgroup reads for itself
-
 struct FlatLaunch {
     int kind;            // 0 flux divergence, 1 super-step group, 2 Euler sub-steps
     const double* T;     // Y0: the stencil input of group 0
@@ -72,12 +67,8 @@ struct FlatLaunch {
     int smin, s_cap;     // s outside [smin, s_cap]: nothing is done
     FlatTiling t;
     GridConst gc;
-    int from;            // kFlat...
-    const double* partials;
-    int npart;
-    double dt_hyp;
-    int mode;            // finalize_state's
-    int32_t* s_out;      // device, may be NULL
+    int derive;          // every workgroup forms the state from src; else *state holds it
+    StateSource src;
     int first, last;     // kind 2: the first reads T, the last writes Tout
     int count;           // kind 2: sub-steps of this launch
     double scale[kFlatEuler];   // kind 2: -tau_k (gamma-1)/rho

@@ -29,7 +29,8 @@ template <typename R, bool LIM, int SAT, int KM, int ND>
 __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double rows[64 * 5];
-    __shared__ double red[3][kFlatThreads / 64];
+    __shared__ double red[3][16];
+    static_assert(kFlatThreads <= 16 * 64, "a slot of red per wave");
     __shared__ GridState sst;
     const int tid = threadIdx.x, nt = blockDim.x;
     const FlatTiling& t = P.t;
@@ -126,54 +127,14 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     }
 
     // dt_par, s and T_ref: the extrema of T, by every workgroup for itself
-    if (P.from != kFlatStateReady) {
-        double mx = -INFINITY, mn = INFINITY, bad = 0.0;
-        if (P.from == kFlatFromField) {
-            for (size_t i = tid; i < N; i += nt) {
-                const double v = P.T[i];
-                mx = fmax(mx, v);
-                mn = fmin(mn, v);
-                bad = isfinite(v) ? bad : 1.0;
-            }
-        } else {
-            for (int i = tid; i < P.npart; i += nt) {
-                mx = fmax(mx, P.partials[3 * i]);
-                mn = fmin(mn, P.partials[3 * i + 1]);
-                bad = fmax(bad, P.partials[3 * i + 2]);
-            }
-        }
-        for (int off = 32; off > 0; off >>= 1) {
-            mx = fmax(mx, __shfl_xor(mx, off));
-            mn = fmin(mn, __shfl_xor(mn, off));
-            bad = fmax(bad, __shfl_xor(bad, off));
-        }
-        if (tid % 64 == 0) {
-            red[0][tid / 64] = mx;
-            red[1][tid / 64] = mn;
-            red[2][tid / 64] = bad;
-        }
+    if (P.derive) {
+        block_state(P.gc, P.src, blockIdx.x == 0, P.state, red, &sst);
+    } else {
+        if (tid == 0) sst = *P.state;
         __syncthreads();
-        if (tid < 64) {
-            for (int i = 0; i < nt / 64; ++i) {
-                mx = fmax(mx, red[0][i]);
-                mn = fmin(mn, red[1][i]);
-                bad = fmax(bad, red[2][i]);
-            }
-            const GridState o = finalize_state(P.gc, mx, mn, bad != 0.0, P.dt_hyp, P.mode, P.s_cap);
-            if (tid == 0) {
-                sst = o;
-                if (blockIdx.x == 0) {
-                    *P.state = o;
-                    if (P.s_out) *P.s_out = o.s;
-                }
-            }
-        }
-    } else if (tid == 0) {
-        sst = *P.state;
     }
-    __syncthreads();
-    const int s = sst.s;
-    const double tref = sizeof(R) == 4 ? sst.tref : 0.0;
+    const int s = __builtin_amdgcn_readfirstlane(sst.s);
+    const double tref = sizeof(R) == 4 ? uniform(sst.tref) : 0.0;
     const FaceK<R> fk = make_facek<R>(P.gc.kappa0, P.gc.kexp, P.gc.kperp, P.gc.satq, tref);
     int j0 = 1, j1 = 1;
     bool last = true;
@@ -184,7 +145,7 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
         j0 = (int)(((long long)s * P.group + G - 1) / G) + 1;
         j1 = (int)(((long long)s * (P.group + 1) + G - 1) / G);
         last = P.group == G - 1;
-        scale = -sst.cdiv;
+        scale = -uniform(sst.cdiv);
     } else if (P.kind == 2) {
         j1 = P.count;
         last = P.last != 0;

@@ -77,6 +77,21 @@ __device__ inline GridState finalize_state(const GridConst& g, double mx, double
     return o;
 }
 
+// What a call that returns a device result to its host caller waits for: the
+// kernel that forms the state stores these words into pinned host memory, and
+// the host polls them while later launches are already enqueued.
+struct HostWords {
+    double dt_par;   // kNoDtPar until written (dt_par is never negative)
+    int32_t s;       // kNoStages until written
+};
+constexpr double kNoDtPar = -1.0;
+constexpr int32_t kNoStages = -0x7fffffff - 1;
+
+__device__ inline void store_host(HostWords* h, const GridState& o) {
+    __hip_atomic_store(&h->dt_par, o.dt_par, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&h->s, o.s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Row j (0 <= j <= s) of the RKL2 coefficient table of an s-stage super-step
 // (Appendix A): w1 = 4/(s^2+s-2), b_j = (j^2+j-2)/(2j(j+1)) (b_0 = b_1 =
 // b_2 = 1/3), a_j = 1 - b_j; row 1 holds mut_1 = b_1 w1 in r[3]; rows
@@ -108,6 +123,94 @@ __host__ __device__ inline void rkl2_row(int s, int j, double* r) {
     }
 }
 
+// Where a workgroup takes the extrema of a grid's T from, and what it does
+// with the state they give: `field` (field_n cells, read whole), else
+// ext_part when *ext_ok is set (the triples that the last stage of the
+// previous super-step wrote), else the reduction's triples `part`.
+constexpr int64_t kFieldCells = 16;   // most cells per thread for `field`: a reduction launch costs as much
+struct StateSource {
+    const double* field;
+    int64_t field_n;
+    const double* part;
+    int npart;
+    const double* ext_part;
+    int ext_n;
+    const int32_t* ext_ok;
+    double dt_hyp;
+    int mode, smax;      // as for finalize_state
+    int32_t* s_out;      // device, may be NULL
+    HostWords* host;     // pinned, may be NULL
+    double* coef_rows;   // may be NULL: rows 0..s of the RKL2 table (2 <= s <= smax) are written there
+};
+
+// a value that is the same in every lane, as a scalar
+__device__ __forceinline__ double uniform(double v) {
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)u), hi = __builtin_amdgcn_readfirstlane((int)(u >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// The state of grid g, the same in every thread of the workgroup (`waves`
+// waves; red and out are LDS).  With `write` (one workgroup of a launch) it
+// also goes to *state and to the caller's places.
+__device__ __forceinline__ void block_state(const GridConst& g, const StateSource& q, bool write, GridState* state,
+                                            double (*red)[16], GridState* out) {
+    const int tid = threadIdx.x, nt = blockDim.x, waves = nt / 64;
+    double mx = -INFINITY, mn = INFINITY, bad = 0.0;
+    if (q.field) {
+        for (int64_t i = tid; i < q.field_n; i += nt) {
+            const double v = q.field[i];
+            mx = fmax(mx, v);
+            mn = fmin(mn, v);
+            bad = isfinite(v) ? bad : 1.0;
+        }
+    } else {
+        const bool ext = q.ext_ok && q.ext_part && *q.ext_ok;   // the same in every lane
+        const double* part = ext ? q.ext_part : q.part;
+        const int n = ext ? q.ext_n : q.npart;
+        for (int i = tid; i < n; i += nt) {
+            mx = fmax(mx, part[3 * i]);
+            mn = fmin(mn, part[3 * i + 1]);
+            bad = fmax(bad, part[3 * i + 2]);
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        mx = fmax(mx, __shfl_xor(mx, off));
+        mn = fmin(mn, __shfl_xor(mn, off));
+        bad = fmax(bad, __shfl_xor(bad, off));
+    }
+    if (tid % 64 == 0) {
+        red[0][tid / 64] = mx;
+        red[1][tid / 64] = mn;
+        red[2][tid / 64] = bad;
+    }
+    __syncthreads();
+    if (tid < 64) {
+        for (int i = 0; i < waves; ++i) {
+            mx = fmax(mx, red[0][i]);
+            mn = fmin(mn, red[1][i]);
+            bad = fmax(bad, red[2][i]);
+        }
+        const GridState o = finalize_state(g, mx, mn, bad != 0.0, q.dt_hyp, q.mode, q.smax);
+        if (write && q.coef_rows && q.mode == 0 && g.scheme == 0 && o.s >= 2 && o.s <= q.smax) {
+            for (int j = tid; j <= o.s; j += 64) {
+                double r[5];
+                rkl2_row(o.s, j, r);
+                for (int i = 0; i < 5; ++i) q.coef_rows[5 * j + i] = r[i];
+            }
+        }
+        if (tid == 0) {
+            *out = o;
+            if (write) {
+                if (q.host) store_host(q.host, o);   // first: the host is waiting
+                *state = o;
+                if (q.s_out) *q.s_out = o.s;
+            }
+        }
+    }
+    __syncthreads();
+}
+
 // Kernel variants of the single-grid stencil: tile shape, z-chunk length and
 // stages per launch (1, or 2 for the fused kernel).
 struct Variant {
@@ -126,28 +229,25 @@ Variant fit_variant(int precision, Variant v, const GridConst& gc);
 hipError_t launch_reduce(const double* T, int64_t N, double* partials, int nblocks, hipStream_t st,
                          const int32_t* skip = nullptr);
 int reduce_blocks(int64_t N);
-// coef_rows (may be NULL): for a super-step (mode 0, RKL2) whose stage count
-// s is in [2, smax], rows 0..s of its coefficient table (rkl2_row, 5 doubles
-// each; room for smax + 1 rows) are written there on the device.
-// ext_ok (may be NULL): when *ext_ok is nonzero on the device and ext_part
-// is given, the extrema are taken from ext_part (ext_nb per-workgroup
-// triples written by the last stage of the previous super-step) instead of
-// `partials`; *ext_ok is cleared either way.
-hipError_t launch_finalize(const double* partials, int nblocks, const GridConst& gc, double dt_hyp,
-                           int mode, GridState* state, int32_t* s_out, int smax, hipStream_t st,
-                           double* coef_rows = nullptr, const double* ext_part = nullptr, int ext_nb = 0,
-                           int32_t* ext_ok = nullptr);
+// one workgroup: the state of grid gc from q, to *state; clears *ext_clear
+// (may be NULL) after q.ext_ok has been read
+hipError_t launch_finalize(const GridConst& gc, const StateSource& q, GridState* state, int32_t* ext_clear,
+                           hipStream_t st);
+// a reduction's partial extrema as the source of a state
+inline StateSource partials_source(const double* part, int npart, double dt_hyp, int mode, int smax, int32_t* s_out) {
+    return StateSource{nullptr, 0, part, npart, nullptr, 0, nullptr, dt_hyp, mode, smax, s_out, nullptr, nullptr};
+}
 // Device-side routing of an RKL2 stage (for launch sequences that do not
 // know s on the host): with s the grid's device-side stage count, stage j
-// does nothing when j > s or s is outside [2, s_cap]; otherwise it reads
-// Y_{j-1} and Y_{j-2} from, and writes Y_j to, T (Y_0 and Y_s), A (odd j)
-// or B (even j).  coef_flat: the coefficient rows of the current s start at
+// does nothing when j > s or s is outside [s_min, s_cap] (s_min 1 for RKL1,
+// else 2); otherwise it reads Y_{j-1} and Y_{j-2} from, and writes Y_j to, T
+// (Y_0 and, for s >= 2, Y_s), A (odd j) or B (even j).  coef_flat: the coefficient rows of the current s start at
 // `coef` (row j at 5 j) instead of the table of all s (row of s at
 // 5 s(s+1)/2).
 struct Route {
     double* A;
     double* B;
-    int s_cap;
+    int s_min, s_cap;
     int coef_flat;
 };
 // Extrema of the last stage (routed sequences, 3-D grids without fixed axes):

@@ -31,7 +31,15 @@ __global__ __launch_bounds__(256) void reduce_minmax_kernel(const double* __rest
                                                             const int32_t* __restrict__ skip) {
     if (skip && *skip) return;   // uniform: the extrema are already there
     double mx = -INFINITY, mn = INFINITY, bad = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N; i += (int64_t)gridDim.x * 256) {
+    const int64_t step = (int64_t)gridDim.x * 256;
+    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (; i + 3 * step < N; i += 4 * step) {   // four loads in flight per lane
+        const double v0 = T[i], v1 = T[i + step], v2 = T[i + 2 * step], v3 = T[i + 3 * step];
+        mx = fmax(mx, fmax(fmax(v0, v1), fmax(v2, v3)));
+        mn = fmin(mn, fmin(fmin(v0, v1), fmin(v2, v3)));
+        bad = isfinite(v0) && isfinite(v1) && isfinite(v2) && isfinite(v3) ? bad : 1.0;
+    }
+    for (; i < N; i += step) {
         const double v = T[i];
         mx = fmax(mx, v);
         mn = fmin(mn, v);
@@ -71,68 +79,17 @@ hipError_t launch_reduce(const double* T, int64_t N, double* partials, int nbloc
     return hipGetLastError();
 }
 
-// mode 0: super-step (computes s); mode 1: flux_div / dt_par only (s = 0).
-// Four waves read the partial extrema; every lane of wave 0 then holds the
-// grid's extrema and forms the same state; lane 0 stores it and the lanes
-// of wave 0 share the rows of the coefficient table (coef_rows, RKL2
-// super-steps with 2 <= s <= smax).
-constexpr int kFinThreads = 256;
-__global__ __launch_bounds__(kFinThreads) void finalize_kernel(const double* __restrict__ part, int nb, GridConst g,
-                                                               double dt_hyp, int mode, GridState* st,
-                                                               int32_t* s_out, int smax, double* coef_rows,
-                                                               const double* __restrict__ ext_part, int ext_nb,
-                                                               int32_t* ext_ok) {
-    if (ext_ok) {
-        const bool use = ext_part && *ext_ok;   // the same in every lane
-        if (use) {
-            part = ext_part;
-            nb = ext_nb;
-        }
-    }
-    double mx = -INFINITY, mn = INFINITY, bad = 0.0;
-    for (int i = threadIdx.x; i < nb; i += kFinThreads) {
-        mx = fmax(mx, part[3 * i]);
-        mn = fmin(mn, part[3 * i + 1]);
-        bad = fmax(bad, part[3 * i + 2]);
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        mx = fmax(mx, __shfl_xor(mx, off));
-        mn = fmin(mn, __shfl_xor(mn, off));
-        bad = fmax(bad, __shfl_xor(bad, off));
-    }
-    __shared__ double sm[3][kFinThreads / 64];
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-    if (l == 0) {
-        sm[0][w] = mx;
-        sm[1][w] = mn;
-        sm[2][w] = bad;
-    }
-    __syncthreads();   // also orders every lane's read of *ext_ok before its clearing below
-    if (w != 0) return;
-    for (int i = 1; i < kFinThreads / 64; ++i) {
-        mx = fmax(mx, sm[0][i]);
-        mn = fmin(mn, sm[1][i]);
-        bad = fmax(bad, sm[2][i]);
-    }
-    const GridState o = finalize_state(g, mx, mn, bad != 0.0, dt_hyp, mode, smax);
-    if (coef_rows && mode == 0 && g.scheme == 0 && o.s >= 2 && o.s <= smax) {
-        for (int j = l; j <= o.s; j += 64) {
-            double r[5];
-            rkl2_row(o.s, j, r);
-            for (int i = 0; i < 5; ++i) coef_rows[5 * j + i] = r[i];
-        }
-    }
-    if (l != 0) return;
-    *st = o;
-    if (s_out) *s_out = o.s;
-    if (ext_ok) *ext_ok = 0;
+__global__ __launch_bounds__(1024) void finalize_kernel(GridConst g, StateSource q, GridState* st,
+                                                        int32_t* ext_clear) {
+    __shared__ double red[3][16];
+    __shared__ GridState o;
+    block_state(g, q, true, st, red, &o);
+    if (ext_clear && threadIdx.x == 0) *ext_clear = 0;   // every lane has read it
 }
 
-hipError_t launch_finalize(const double* partials, int nblocks, const GridConst& gc, double dt_hyp,
-                           int mode, GridState* state, int32_t* s_out, int smax, hipStream_t st,
-                           double* coef_rows, const double* ext_part, int ext_nb, int32_t* ext_ok) {
-    finalize_kernel<<<1, kFinThreads, 0, st>>>(partials, nblocks, gc, dt_hyp, mode, state, s_out, smax, coef_rows,
-                                               ext_part, ext_nb, ext_ok);
+hipError_t launch_finalize(const GridConst& gc, const StateSource& q, GridState* state, int32_t* ext_clear,
+                           hipStream_t st) {
+    finalize_kernel<<<1, q.field || q.ext_n > 1024 ? 1024 : 256, 0, st>>>(gc, q, state, ext_clear);
     return hipGetLastError();
 }
 
@@ -244,7 +201,7 @@ hipError_t launch_stage(int precision, Variant v, const GridConst& gc, int kind,
     P.kmode = gc.kmode;
     P.fac = gc.fac;
     P.sub_scale = sub_scale;
-    P.route = Route{nullptr, nullptr, 0, 0};
+    P.route = Route{nullptr, nullptr, 0, 0, 0};
     P.ext = ExtOut{nullptr, nullptr};
     if (ext) {
         // the last-stage extrema: routed RKL2 stages of 3-D grids without fixed axes

@@ -116,18 +116,20 @@ extern "C" rkl_status rkl_superstep_noalloc(const rkl_grid_desc* grid, int32_t p
         P.s_cap = s_cap;
         P.t = ft;
         P.gc = gc;
-        P.dt_hyp = dt_hyp;
-        P.s_out = s_out;
-        P.partials = part;
-        P.npart = std::min(reduce_blocks(N), 256);
-        P.from = N <= kFlatFieldCells ? kFlatFromField : kFlatFromPartials;
-        if (P.from == kFlatFromPartials) {
-            const hipError_t re = launch_reduce(T, N, part, P.npart, s);
+        P.derive = 1;
+        if (N <= kFieldCells * ft.threads) {
+            P.src = partials_source(nullptr, 0, dt_hyp, 0, s_cap, s_out);
+            P.src.field = T;
+            P.src.field_n = N;
+        } else {
+            const int np = std::min(reduce_blocks(N), 256);
+            const hipError_t re = launch_reduce(T, N, part, np, s);
             if (re != hipSuccess) return hipfail(re, "reduce launch");
+            P.src = partials_source(part, np, dt_hyp, 0, s_cap, s_out);
         }
         for (int k = 0; k < P.groups; ++k) {
             P.group = k;
-            if (k > 0) P.from = kFlatStateReady;
+            if (k > 0) P.derive = 0;
             const int o = k % 2 == 0 ? 0 : 2, i = 2 - o;
             P.out1 = f + o * N;
             P.out2 = f + (o + 1) * N;
@@ -138,15 +140,21 @@ extern "C" rkl_status rkl_superstep_noalloc(const rkl_grid_desc* grid, int32_t p
         }
         return RKL_OK;
     }
-    const int nb = reduce_blocks(N);
-    hipError_t e = launch_reduce(T, N, part, nb, s);
-    if (e != hipSuccess) return hipfail(e, "reduce launch");
     // dt_par, s and the coefficient rows of s on the device; s > s_cap flags
     // the grid and every stage below returns at once
-    e = launch_finalize(part, nb, gc, dt_hyp, 0, state, s_out, s_cap, s, coef);
-    if (e != hipSuccess) return hipfail(e, "finalize launch");
-    const Route r{A, B, s_cap, 1};
     const Variant v = fit_variant(precision, variant_get(kDefaultVariant), gc);
+    const int nb = reduce_blocks(N);
+    StateSource src = partials_source(part, nb, dt_hyp, 0, s_cap, s_out);
+    hipError_t e = hipSuccess;
+    if (N <= kFieldCells * 1024) {
+        src.field = T;
+        src.field_n = N;
+    } else if ((e = launch_reduce(T, N, part, nb, s)) != hipSuccess) {
+        return hipfail(e, "reduce launch");
+    }
+    src.coef_rows = coef;
+    if ((e = launch_finalize(gc, src, state, nullptr, s)) != hipSuccess) return hipfail(e, "finalize launch");
+    const Route r{A, B, 2, s_cap, 1};
     for (int j = 1; j <= s_cap; ++j) {
         e = launch_stage(precision, v, gc, j == 1 ? 1 : 2, j, nullptr, nullptr, nullptr, M, M, T, b,
                          state, coef, s, 0.0, &r);

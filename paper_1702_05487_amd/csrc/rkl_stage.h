@@ -55,7 +55,7 @@ __global__ __launch_bounds__(BX* BY) void stage_kernel(StageLaunch P) {
         const int s = st->s;
         if (P.route.A) {
             // the stage sequence was launched up to s_cap without knowing s
-            if (P.stage > s || s < 2 || s > P.route.s_cap) return;   // uniform over the grid
+            if (P.stage > s || s < P.route.s_min || s > P.route.s_cap) return;   // uniform over the grid
             const int j = P.stage;
             double* T = a.Yout;   // the caller's T (Y_0, and Y_s)
             double* Yj = (j & 1) ? P.route.A : P.route.B;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(BX* BY) void stage_kernel(StageLaunch P) {
                 a.Yin = ((j - 1) & 1) ? P.route.A : P.route.B;
                 a.Ym2 = j == 2 ? T : Yj;   // Y_{j-2} sits where Y_j goes
             }
-            a.Yout = j == s ? T : Yj;
+            a.Yout = j == s && j > 1 ? T : Yj;   // stage 1 reads T around each cell
             a.ext = MODE == 1 && P.ext.part && j == s;
         }
         const double* cf = P.coef + 5 * (P.route.coef_flat ? (size_t)P.stage : (size_t)s * (s + 1) / 2 + P.stage);
