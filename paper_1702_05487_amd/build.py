@@ -16,7 +16,7 @@ OBJ = os.path.join(os.path.dirname(HERE), "_build")
 LIB = os.path.join(HERE, "librkl.so")
 SOURCES = ["rkl_stage_f64_32x8.hip", "rkl_stage_f64_64x4.hip", "rkl_stage_f64_16x16.hip",
            "rkl_stage_f32_32x8.hip", "rkl_stage_f32_64x4.hip", "rkl_stage_f32_16x16.hip",
-           "rkl_flat_f64.hip", "rkl_flat_f32.hip", "rkl_flat.hip",
+           "rkl_flat_f64.hip", "rkl_flat_f32.hip", "rkl_block_f64.hip", "rkl_block_f32.hip", "rkl_flat.hip",
            "rkl_kernels.hip", "rkl_fused.hip", "rkl_batch.hip", "rkl_api.hip", "rkl_noalloc.hip", "rkl_stream.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

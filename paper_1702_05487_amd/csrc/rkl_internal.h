@@ -215,7 +215,9 @@ __device__ __forceinline__ void block_state(const GridConst& g, const StateSourc
 // stages per launch (1, or 2 for the fused kernel).
 struct Variant {
     int bx, by, bz, fuse;
+    bool block = false;   // fitted: blocks of bx x by x bz cells (rkl_block.h) instead of z-marched tiles
 };
+constexpr int kBlockX = 16, kBlockY = 4, kBlockZ = 4;
 int variant_count();
 Variant variant_get(int v);
 constexpr int kDefaultVariant = 1;   // 32 x 8 tile, z-chunks of at most 64 planes

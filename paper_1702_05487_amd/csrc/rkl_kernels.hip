@@ -96,8 +96,10 @@ hipError_t launch_finalize(const GridConst& gc, const StateSource& q, GridState*
 // -------------------------------------------------------- stage kernels ----
 // (instantiated in the rkl_stage_*.hip units)
 template <typename R>
-static hipError_t launch_prec(const StageLaunch& P, int nblocks, int bx, int by, bool lim, int sat,
+static hipError_t launch_prec(const StageLaunch& P, int nblocks, const Variant& v, bool lim, int sat,
                               hipStream_t st) {
+    if (v.block) return launch_block<R>(P, nblocks, lim, sat, st);
+    const int bx = v.bx, by = v.by;
     // grids with fixed axes: one runtime-shaped 16 x 16 kernel with the ghost loads
     if (P.t.fixed) return bx == 16 && by == 16 ? launch_fixed<R>(P, nblocks, lim, sat, st)
                                                : hipErrorInvalidValue;
@@ -107,27 +109,35 @@ static hipError_t launch_prec(const StageLaunch& P, int nblocks, int bx, int by,
     return hipErrorInvalidValue;
 }
 
-// Planes per workgroup of a one-stage launch on a 3-D grid.  A workgroup
-// marches its z-chunk plane after plane, each plane a chain of one barrier,
-// LDS exchanges and three face evaluations, so a launch takes as long as its
-// longest march times the rounds of resident workgroups.  A chunk of bz
-// planes costs bz + 2 plane iterations (the two before z0 fill the rings);
-// an iteration takes c[k] microseconds with k workgroups on a CU (MC, T^2.5
-// and saturated flux; measured with 64^3 to 192^3 grids, k = 1, 2, 3; three
-// mixed or two FP64 workgroups fit a CU's registers).  Short chunks give a
-// small grid enough workgroups for the 256 CUs, long ones keep the two extra
-// iterations and the halo planes cheap.  Measured per stage, 32 x 8 tile,
-// the variant's own 32 planes against the chunk taken here: 45 x 33 x 29 FP64
-// 37.8 -> 8.8 us, 64^3 mixed 38.0 -> 8.8 us, 128^3 FP64 50.7 -> 39.3 us,
-// 150 x 127 x 101 mixed 45.2 -> 28.9 us.  The last, partly filled round is
-// priced half by its share of the slots and half as a round of its own:
-// workgroups of different rounds overlap, but not fully.
+// How a one-stage launch on a 3-D grid is split.
+//
+// Marched tiles (run_tile): a workgroup marches its z-chunk plane after plane,
+// each plane a chain of one barrier, LDS exchanges and three face evaluations,
+// so a launch takes as long as its longest march times the rounds of resident
+// workgroups.  A chunk of bz planes costs bz + 2 plane iterations (the two
+// before z0 fill the rings); an iteration takes c[k] microseconds with k
+// workgroups on a CU (MC, T^2.5 and saturated flux; measured with 64^3 to
+// 192^3 grids, k = 1, 2, 3; three mixed or two FP64 workgroups fit a CU's
+// registers), and a launch 4 us besides.  Short chunks give a small grid enough
+// workgroups for the 256 CUs, long ones keep the two extra iterations and the
+// halo planes cheap.  The last, partly filled round is priced half by its share
+// of the slots and half as a round of its own: workgroups of different rounds
+// overlap, but not fully.
+//
+// Blocks of 16 x 4 x 4 cells (rkl_block.h): no march, so the least a launch
+// takes is 5.4 us (FP64; mixed 5.0), but 0.0056 us (0.0035) more per block
+// against 0.0025 (0.0016) for 256 marched cells of a large grid.
+//
+// Measured per stage, 32-plane chunks / the chunk taken here / blocks:
+// 45 x 33 x 29 FP64 37.8 / 9.0 / 5.5 us, 64^3 mixed 38.0 / 9.4 / 7.4 us, 64^3
+// FP64 49.3 / 12.5 / 9.8 us, 96^3 FP64 49.9 / 23.5 / 24.1 us, 128^3 FP64 50.7 /
+// 42.4 / 50.1 us, 150 x 127 x 101 mixed 45.2 / 30.3 / 33.4 us.
 Variant fit_variant(int precision, Variant v, const GridConst& gc) {
     if (gc.fixed) v = Variant{16, 16, v.bz, 1};   // the tile shape of the ghost-loading kernel
-    if (gc.n2 == 1) return v;
-    const int per_cu = precision == RKL_MIXED ? 3 : 2;
+    const bool f32 = precision == RKL_MIXED;
+    const int per_cu = f32 ? 3 : 2;
     static const double c32[] = {0.0, 1.03, 1.3, 1.6}, c64[] = {0.0, 1.3, 1.95};
-    const double* c = precision == RKL_MIXED ? c32 : c64;
+    const double* c = f32 ? c32 : c64;
     const int64_t tiles = (int64_t)((gc.n0 + v.bx - 1) / v.bx) * ((gc.n1 + v.by - 1) / v.by);
     const int64_t slots = 256 * per_cu;
     int best = v.bz;
@@ -149,6 +159,12 @@ Variant fit_variant(int precision, Variant v, const GridConst& gc) {
         }
     }
     v.bz = best;
+    if (gc.ndim == 3 && !gc.fixed && (int64_t)gc.n0 * gc.n1 * gc.n2 < (int64_t)1 << 29) {   // 32-bit byte offsets
+        Variant w{kBlockX, kBlockY, kBlockZ, 1, true};
+        const double nb = (double)stage_blocks(w, gc);
+        const double block = f32 ? std::max(5.0, 4.0 + 0.0035 * nb) : std::max(5.4, 4.1 + 0.0056 * nb);
+        if (block < 4.0 + c[per_cu] * best_cost) return w;
+    }
     return v;
 }
 
@@ -220,8 +236,8 @@ hipError_t launch_stage(int precision, Variant v, const GridConst& gc, int kind,
     if (nb <= 0 || nb > 0x7fffffff) return hipErrorInvalidValue;
     const bool lim = gc.limiter != 0;
     const int sat = gc.saturation;
-    if (precision == RKL_MIXED) return launch_prec<float>(P, (int)nb, v.bx, v.by, lim, sat, st);
-    return launch_prec<double>(P, (int)nb, v.bx, v.by, lim, sat, st);
+    if (precision == RKL_MIXED) return launch_prec<float>(P, (int)nb, v, lim, sat, st);
+    return launch_prec<double>(P, (int)nb, v, lim, sat, st);
 }
 
 }  // namespace rkl

@@ -23,6 +23,76 @@ struct StageLaunch {
     ExtOut ext;          // ext.part != NULL: the launch of stage j = s keeps the extrema of Y_s
 };
 
+// The buffers a routed stage reads, which follow from j alone, so that loads
+// need not wait for the state: Y_{j-1} and Y_{j-2} (a.Yout: the caller's T,
+// Y_0 and Y_s).
+__device__ __forceinline__ void stage_inputs(const StageLaunch& P, TileArgs& a) {
+    const int j = P.stage;
+    if (!P.route.A || a.kind == 0 || a.kind == 3 || j == 1) return;   // stage 1 reads T
+    a.Yin = ((j - 1) & 1) ? P.route.A : P.route.B;
+    a.Ym2 = j == 2 ? a.Yout : (j & 1) ? P.route.A : P.route.B;   // Y_{j-2} sits where Y_j goes
+}
+
+// The output and the coefficients of this launch, with s and cdiv of the
+// grid's state; false where a routed stage does nothing, uniform over the
+// grid.  ext_able: the kernel can keep the extrema of the last stage.
+__device__ __forceinline__ bool stage_args(const StageLaunch& P, bool ext_able, int s, double cdiv, TileArgs& a) {
+    if (a.kind == 0) {
+        a.scale = -P.fac;
+    } else if (a.kind == 3) {
+        a.scale = P.sub_scale;
+    } else {
+        if (P.route.A) {
+            // the stage sequence was launched up to s_cap without knowing s
+            const int j = P.stage;
+            if (j > s || s < P.route.s_min || s > P.route.s_cap) return false;
+            // Y_s goes to T, but not from stage 1, which reads T around each cell
+            if (j < s || j == 1) a.Yout = (j & 1) ? P.route.A : P.route.B;
+            a.ext = ext_able && P.ext.part && j == s;
+        }
+        const double* cf = P.coef + 5 * (P.route.coef_flat ? (size_t)P.stage : (size_t)s * (s + 1) / 2 + P.stage);
+        a.mu = cf[0];
+        a.nu = cf[1];
+        a.omn = cf[2];
+        a.mut = cf[3];
+        a.gt = cf[4];
+        a.scale = -cdiv;
+    }
+    return true;
+}
+
+// the extrema of Y_s of a workgroup of NT threads, as one block of the reduction pass
+template <int NT>
+__device__ __forceinline__ void store_ext(const StageLaunch& P, const TileExt& e) {
+    double mx = e.mx, mn = e.mn, bad = e.bad;
+    for (int off = 32; off > 0; off >>= 1) {
+        mx = fmax(mx, __shfl_xor(mx, off));
+        mn = fmin(mn, __shfl_xor(mn, off));
+        bad = fmax(bad, __shfl_xor(bad, off));
+    }
+    constexpr int NW = NT / 64;
+    __shared__ double esm[3][NW];
+    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
+    if (l == 0) {
+        esm[0][w] = mx;
+        esm[1][w] = mn;
+        esm[2][w] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < NW; ++i) {
+            mx = fmax(mx, esm[0][i]);
+            mn = fmin(mn, esm[1][i]);
+            bad = fmax(bad, esm[2][i]);
+        }
+        double* o = P.ext.part + 3 * (size_t)blockIdx.x;
+        o[0] = mx;
+        o[1] = mn;
+        o[2] = bad;
+        if (blockIdx.x == 0) *P.ext.ok = 1;   // read after this launch ends
+    }
+}
+
 // MODE 1: 3-D grid, tile shape fixed at compile time (run_tile's CBX, CBY);
 // MODE 0: runtime tile shape; MODE 2: runtime tile shape with the ghost
 // layers of fixed axes
@@ -43,73 +113,14 @@ __global__ __launch_bounds__(BX* BY) void stage_kernel(StageLaunch P) {
     a.y0 = tile_y * BY;
     a.z0 = zc * P.bz;
     a.z1 = min(a.z0 + P.bz, a.n2);
-
-    const GridState* st = P.state;
-    double tref = 0.0;
-    if (sizeof(R) == 4) tref = st->tref;
-    if (a.kind == 0) {
-        a.scale = -P.fac;
-    } else if (a.kind == 3) {
-        a.scale = P.sub_scale;
-    } else {
-        const int s = st->s;
-        if (P.route.A) {
-            // the stage sequence was launched up to s_cap without knowing s
-            if (P.stage > s || s < P.route.s_min || s > P.route.s_cap) return;   // uniform over the grid
-            const int j = P.stage;
-            double* T = a.Yout;   // the caller's T (Y_0, and Y_s)
-            double* Yj = (j & 1) ? P.route.A : P.route.B;
-            if (j == 1) {
-                a.Yin = T;
-            } else {
-                a.Yin = ((j - 1) & 1) ? P.route.A : P.route.B;
-                a.Ym2 = j == 2 ? T : Yj;   // Y_{j-2} sits where Y_j goes
-            }
-            a.Yout = j == s && j > 1 ? T : Yj;   // stage 1 reads T around each cell
-            a.ext = MODE == 1 && P.ext.part && j == s;
-        }
-        const double* cf = P.coef + 5 * (P.route.coef_flat ? (size_t)P.stage : (size_t)s * (s + 1) / 2 + P.stage);
-        a.mu = cf[0];
-        a.nu = cf[1];
-        a.omn = cf[2];
-        a.mut = cf[3];
-        a.gt = cf[4];
-        a.scale = -st->cdiv;
-    }
+    stage_inputs(P, a);
+    const double tref = sizeof(R) == 4 ? P.state->tref : 0.0;
+    if (!stage_args(P, MODE == 1, P.state->s, P.state->cdiv, a)) return;
     const FaceK<R> fk = make_facek<R>(P.kappa0, P.kexp, P.kperp, P.satq, tref);
     if constexpr (MODE == 1) {
         const TileExt e =
             run_tile<R, LIM, SAT, KM, PL, (BX + 1) * BY, BX*(BY + 1), BX, BY, false, 6, true>(a, fk, tref, L);
-        if (a.ext) {   // uniform: the last stage of a routed sequence
-            // the workgroup's extrema of Y_s, as one block of the reduction pass
-            double mx = e.mx, mn = e.mn, bad = e.bad;
-            for (int off = 32; off > 0; off >>= 1) {
-                mx = fmax(mx, __shfl_xor(mx, off));
-                mn = fmin(mn, __shfl_xor(mn, off));
-                bad = fmax(bad, __shfl_xor(bad, off));
-            }
-            constexpr int NW = BX * BY / 64;
-            __shared__ double esm[3][NW];
-            const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-            if (l == 0) {
-                esm[0][w] = mx;
-                esm[1][w] = mn;
-                esm[2][w] = bad;
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                for (int i = 1; i < NW; ++i) {
-                    mx = fmax(mx, esm[0][i]);
-                    mn = fmin(mn, esm[1][i]);
-                    bad = fmax(bad, esm[2][i]);
-                }
-                double* o = P.ext.part + 3 * (size_t)blockIdx.x;
-                o[0] = mx;
-                o[1] = mn;
-                o[2] = bad;
-                if (blockIdx.x == 0) *P.ext.ok = 1;   // read after this launch ends
-            }
-        }
+        if (a.ext) store_ext<BX * BY>(P, e);   // uniform: the last stage of a routed sequence
     } else if constexpr (MODE == 2)
         run_tile<R, LIM, SAT, KM, PL, (BX + 1) * BY, BX*(BY + 1), 0, 0, true>(a, fk, tref, L);
     else
@@ -163,5 +174,9 @@ extern template hipError_t launch_shape<double, 64, 4>(RKL_SHAPE_ARGS);
 extern template hipError_t launch_shape<double, 16, 16>(RKL_SHAPE_ARGS);
 extern template hipError_t launch_fixed<float>(RKL_SHAPE_ARGS);
 extern template hipError_t launch_fixed<double>(RKL_SHAPE_ARGS);
+template <typename R>
+hipError_t launch_block(const StageLaunch& P, int nblocks, bool lim, int sat, hipStream_t st);
+extern template hipError_t launch_block<float>(RKL_SHAPE_ARGS);
+extern template hipError_t launch_block<double>(RKL_SHAPE_ARGS);
 
 }  // namespace rkl

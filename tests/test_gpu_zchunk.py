@@ -10,6 +10,11 @@ plane loop in one chunk, and chunks of unequal work at 33 and 65 planes.
     (the bars of the other super-step tests), the same stage count;
   - every depth: the same bits with chunks of at most 16, 32 and 64 planes,
     and from rkl_superstep_async.
+
+Grids of about 130 cells a side march too (smaller ones run in blocks of
+16 x 4 x 4 cells): with ragged sides, every kind of z and x edge and every
+saturation form against the oracle, and chained super-steps, whose last stage
+keeps the extrema, against separate calls.
 """
 import numpy as np
 import pytest
@@ -54,3 +59,35 @@ def test_long_chunks(precision, depth):
         oracle.set_threads(1)
         assert s == 4
         assert rel_l1(got[6], ref) <= (1e-12 if precision == "fp64" else 1e-5)
+
+
+@pytest.mark.parametrize("edges,lim,sat,law,precision", [
+    ((0, 0, 0), 1, 1, 2.5, "fp64"), ((1, 0, 1), 0, 2, 0.0, "mixed"), ((0, 1, 1), 1, 0, 1.7, "fp64"),
+    ((1, 1, 0), 1, 2, 2.5, "mixed"),
+])
+def test_marched_ragged(edges, lim, sat, law, precision):
+    import torch
+    from paper_1702_05487_amd import rkl
+    print("marched", edges, lim, sat, law, precision, flush=True)
+    n = (131, 126, 129)
+    rng = np.random.default_rng(77)
+    T = 1.0 + 0.2 * rng.random(n[::-1])
+    b = inputs.unit_vectors(rng.standard_normal((3,) + n[::-1]))
+    p = dict(inputs.BASE, limiter=lim, saturation=sat, phi=0.01, kappa_exp=law, kperp_ratio=0.02, boundary=edges)
+    g = oracle_grid(n, H, 3, p)
+    dt = inputs.midpoint_ratio(4) * oracle.dt_par(g, T)
+    bd = torch.from_numpy(b).to("cuda:0", torch.float32 if precision == "mixed" else torch.float64)
+    plan = rkl.Plan([lib_desc(n, H, 3, p)], precision=precision)
+    Td = torch.from_numpy(T).to("cuda:0")
+    assert plan.superstep(Td, bd, dt) == 4
+    oracle.set_threads(16)
+    ref, s, _ = oracle.superstep(g, T, bd.double().cpu().numpy(), dt)
+    oracle.set_threads(1)
+    assert s == 4
+    assert rel_l1(Td.cpu().numpy(), ref) <= (1e-12 if precision == "fp64" else 1e-5)
+    many = torch.from_numpy(T).to("cuda:0")
+    plan.supersteps_async(many, bd, dt, 3, 6)
+    for _ in range(2):
+        plan.superstep(Td, bd, dt)
+    assert torch.equal(Td, many)
+    plan.close()
