@@ -385,7 +385,8 @@ rkl_status rkl_autotune(rkl_plan_t plan, int32_t grid, const double *T, const vo
 
 /*
  * Tile policies of the batched launch: rkl_batch_policy_count() of them.
- * rkl_batch_policy_info gives a policy's z-chunk length (tile_z planes) and
+ * rkl_batch_policy_info gives a policy's longest z-chunk (tile_z planes; a
+ * batch too small to fill the GPU with them takes shorter ones) and
  * whether grids wider than 32 cells are split into half-width rows
  * (half_rows 1) instead of full-width ones (any pointer may be NULL).
  * rkl_set_batch_policy selects one for a plan (policy 0 by default); a graph

@@ -35,6 +35,7 @@
 // tiles); every tile runs the same run_tile code as the single-grid kernels,
 // so neither the policy nor the mode changes the result.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <numeric>
 
@@ -385,13 +386,57 @@ void batch_policy_info(int policy, int* half_rows, int* bz) {
     *bz = kPolicies[policy].bz;
 }
 
-static void choose_tile(const GridConst& g, int policy, int plcap, int& bx, int& by, int& bz) {
+static void choose_tile(const GridConst& g, int policy, int plcap, int zmax, int& bx, int& by, int& bz) {
     const BatchPolicy& P = kPolicies[policy];
     bx = std::min(g.n0, 64);
     if (P.half_rows && g.n0 > 32) bx = std::min((g.n0 + 1) / 2, 32);
     by = std::min(std::min(g.n1, kBT / bx), 64);
     while (by > 1 && (bx + 2) * (by + 2) > plcap) --by;
-    bz = std::min(g.n2, P.bz);
+    const int nzc = (g.n2 + zmax - 1) / zmax;
+    bz = (g.n2 + nzc - 1) / nzc;   // chunks of equal length, at most zmax planes
+}
+
+// The longest z-chunk of a batch, at most the policy's: a stage launch lasts
+// as long as its longest march (bz + 2 plane iterations) while all workgroups
+// are resident, and otherwise as all plane iterations take on the slots, plus
+// half a march at the end; so a few small grids take short chunks, which give
+// every CU workgroups, and many take long ones.  The stage counts are not
+// known here: the cost is averaged over launches of stages that all, 0.7, 0.4
+// and 0.1 of the grids still run.  c[k]: microseconds of a plane
+// iteration with k workgroups on a CU (four mixed or three FP64 ones fit).
+// Measured per batched super-step (s to 30), the policy's 32 planes against
+// the chunk taken here: 10 grids of 12 to 50 cells a side, mixed, 1293 -> 311 us;
+// 134 of 14 to 55 1795 -> 1314 us; 2000 of 16 to 64 16.8 -> 16.3 ms.
+static int longest_chunk(const std::vector<GridConst>& gc, int policy, int plcap, bool f32) {
+    static const double c32[] = {0.0, 1.2, 1.4, 1.65, 1.95}, c64[] = {0.0, 1.5, 2.0, 2.5};
+    const double* c = f32 ? c32 : c64;
+    const int per_cu = f32 ? 4 : 3;
+    int best = kPolicies[policy].bz, deepest = 1;
+    for (const GridConst& g : gc) deepest = std::max(deepest, g.n2);
+    double cost = INFINITY;
+    for (int z = std::min(best, deepest); z >= 1; z -= z > 8 ? 2 : 1) {
+        int64_t tiles = 0, work = 0;   // work: plane iterations of all tiles
+        int longest = 1;
+        for (const GridConst& g : gc) {
+            int bx, by, bz;
+            choose_tile(g, policy, plcap, z, bx, by, bz);
+            const int64_t columns = (int64_t)((g.n0 + bx - 1) / bx) * ((g.n1 + by - 1) / by), nzc = (g.n2 + bz - 1) / bz;
+            tiles += columns * nzc;
+            work += columns * (g.n2 + 2 * nzc);
+            longest = std::max(longest, bz + 2);
+        }
+        const int64_t slots = 256 * per_cu;
+        double t = 0.0;
+        for (const double f : {1.0, 0.7, 0.4, 0.1}) {
+            const int64_t live = std::max<int64_t>(1, (int64_t)(f * tiles));
+            t += live <= slots ? c[(live + 255) / 256] * longest : c[per_cu] * (f * work / slots + 0.5 * longest);
+        }
+        if (t < cost) {
+            cost = t;
+            best = z;
+        }
+    }
+    return best;
 }
 
 rkl_status batch_create(const std::vector<rkl_grid_desc>& desc, const std::vector<GridConst>& gc,
@@ -408,6 +453,7 @@ rkl_status batch_create(const std::vector<rkl_grid_desc>& desc, const std::vecto
     const int fycap = f32 ? Cap<float>::FY : Cap<double>::FY;
     const int n = (int)desc.size();
     std::vector<BatchGrid> h(n);
+    const int zmax = longest_chunk(gc, policy, plcap, f32);
     int64_t items = 0;
     for (int g = 0; g < n; ++g) {
         if (desc[g].limiter != desc[0].limiter || desc[g].saturation != desc[0].saturation ||
@@ -419,7 +465,7 @@ rkl_status batch_create(const std::vector<rkl_grid_desc>& desc, const std::vecto
         BatchGrid& B = h[g];
         B.gc = gc[g];
         B.off = off[g];
-        choose_tile(gc[g], policy, plcap, B.bx, B.by, B.bz);
+        choose_tile(gc[g], policy, plcap, zmax, B.bx, B.by, B.bz);
         if ((B.bx + 2) * (B.by + 2) > plcap || (B.bx + 1) * B.by > fxcap || B.bx * (B.by + 1) > fycap ||
             2 * B.bx + 2 * B.by + 4 > kBT) {
             why = "internal: batched tile shape exceeds the LDS layout";
