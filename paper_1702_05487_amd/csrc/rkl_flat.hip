@@ -9,23 +9,28 @@
 
 namespace rkl {
 
-// Microseconds per stage of a grid cut by tiling t and run f stages per
-// launch.  Measured (one MI355X, 20 back-to-back super-steps): a launch costs
-// about 2 us, each round of resident workgroups 2.2 us (1-D) or 4 us (2-D) of
-// loads and set-up, and a stage 0.45 us of dependent latency plus the issue
-// time of the waves that share a SIMD, which grows with the work of a face.
-// The registers allow four waves per SIMD, one workgroup of 1024 threads.
+// Microseconds per stage of a grid cut by tiling t.  Measured (one MI355X, 20
+// back-to-back super-steps): a launch costs about 2 us, each round of resident
+// workgroups 2.2 us (1-D) or 4 us (2-D) of loads and set-up, and a stage 0.45 us
+// of dependent latency plus the issue time of the waves that share a SIMD,
+// which grows with the work of a face.  The registers allow four waves per
+// SIMD, one workgroup of 1024 threads.  The stage count is not known here, and
+// several regions take two launches at least, so no more than 10 (1-D: 14)
+// stages are priced together; one region runs all stages (24 priced) at once.
 // Measured per super-step against one stage per launch: 400 cells (s = 20)
-// 120 -> 17 us, 64 x 64 (14) 85 -> 24 us, 200 x 200 MC (20) 130 -> 46 us;
-// 1024 x 1024 mixed, MC and saturation, 34.7 -> 21.5 us per stage.
-static double flat_cost(int precision, const GridConst& gc, const FlatTiling& t, int f) {
-    const bool f32 = precision == RKL_MIXED;
-    const double face = f32 ? 0.05 + 0.03 * (gc.limiter != 0) + 0.05 * (gc.saturation != 0) + (gc.kmode == 1 ? 0.03 : 0.1 * (gc.kmode == 2))
-                            : 0.08 + 0.03 * (gc.limiter != 0) + 0.08 * (gc.saturation != 0) + (gc.kmode == 1 ? 0.06 : 0.3 * (gc.kmode == 2));
-    const double setup = gc.ndim == 2 ? 4.0 : 2.2;
+// 120 -> 17 us, 64 x 64 (14) 85 -> 23 us, 200 x 200 MC (20) 130 -> 42 us;
+// 1024 x 1024 mixed, MC and saturation, 34.7 -> 18.3 us per stage.
+static double flat_cost(int precision, const GridConst& gc, const FlatTiling& t) {
+    const bool f32 = precision == RKL_MIXED, sat = gc.saturation != 0, lim = gc.limiter != 0;
+    const bool km1 = gc.kmode == 1, km2 = gc.kmode == 2, two = gc.ndim == 2;
+    const double face = !two ? (f32 ? 0.04 + 0.03 * sat : 0.05 + 0.05 * sat) + (km2 ? 0.2 : 0.0)
+                        : f32 ? 2 * (0.05 + 0.03 * lim + 0.05 * sat + 0.03 * km1 + 0.1 * km2)
+                              : 2 * (0.08 + 0.03 * lim + 0.08 * sat + 0.06 * km1 + 0.3 * km2);
+    const double setup = two ? 4.0 : 2.2;
+    const int f = t.blocks() == 1 ? 24 : std::min(t.f, two ? 10 : 14);
     const int waves = t.threads / 64, per_cu = std::max(1, 16 / waves);
     const int64_t nb = t.blocks(), slots = 256 * per_cu, full = nb / slots, rem = nb % slots;
-    const auto round = [&](int64_t wgs) { return setup + f * (0.45 + face * gc.ndim * ((wgs * waves + 3) / 4)); };
+    const auto round = [&](int64_t wgs) { return setup + f * (0.45 + face * ((wgs * waves + 3) / 4)); };
     double tm = 2.0 + full * round(per_cu);
     if (rem) tm += round((rem + 255) / 256);
     return tm / f;
@@ -60,14 +65,13 @@ FlatTiling flat_tiling(int precision, const GridConst& gc) {
     const auto take = [&](int w, int h, int f) {
         const FlatTiling t = shape(gc, w, h, f);
         if (!t.f) return;
-        const double c = flat_cost(precision, gc, t, t.blocks() == 1 ? 20 : std::min(f, 10));
+        const double c = flat_cost(precision, gc, t);
         if (c < cost) {
             cost = c;
             best = t;
         }
     };
-    // one region: every stage in one launch (20 of them priced); several: at
-    // least two launches, so no more than 10 stages priced together
+    // one region: every stage in one launch
     if ((int64_t)gc.n0 * gc.n1 <= kFlatThreads) take(gc.n0, gc.n1, kFlatEuler);
     if (gc.ndim == 1) {
         for (int w : {256, 512, 1008})

@@ -23,8 +23,19 @@ __device__ __forceinline__ R flat_slope(R t) {
     return LIM ? R(0) : t - t;
 }
 
+// the index of cell i of a periodic axis, -n <= i < 2n
+__device__ __forceinline__ int wrap_once(int i, int n) {
+    i = i < 0 ? i + n : i;
+    return i >= n ? i - n : i;
+}
+// element i of a field of at most 2^26 cells: a scalar base and a 32-bit byte offset
+template <typename E>
+__device__ __forceinline__ E ld(const E* base, unsigned i) {
+    return *(const E*)((const char*)base + i * (unsigned)sizeof(E));
+}
+
 // ND: dimensions (1 or 2).  One cell per thread, three barriers a stage (two
-// in 1-D).
+// in 1-D).  The state and every input are asked for before anything waits.
 template <typename R, bool LIM, int SAT, int KM, int ND>
 __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -33,6 +44,9 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     static_assert(kFlatThreads <= 16 * 64, "a slot of red per wave");
     __shared__ GridState sst;
     const int tid = threadIdx.x, nt = blockDim.x;
+    // the state as a former launch left it (the group that forms it does not use these)
+    int s = P.state->s;
+    double tref = P.state->tref, cdiv = P.state->cdiv;
     const FlatTiling& t = P.t;
     const int n0 = P.gc.n0, n1 = P.gc.n1;
     const bool ox = P.gc.bc & 1, oy = P.gc.bc & 2, fx = P.gc.fixed & 1, fy = P.gc.fixed & 2;
@@ -50,12 +64,13 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     if (t.nt1 == 1) { lo1 = 0; hi1 = n1; }
     else if (oy) { lo1 = max(lo1, 0); hi1 = min(hi1, n1); }
     const int w0 = hi0 - lo0, h1 = hi1 - lo1;
-    const int tx = tid % w, ty = tid / w;
+    // tid / w: the quotient is at least 0.5 / w from an integer, far more than its error
+    const int ty = (int)(((float)tid + 0.5f) * __builtin_amdgcn_rcpf((float)w)), tx = tid - ty * w;
     const bool act = tx < w0 && ty < h1;
     const int slot = act ? tid : 0;
     const int gx = act ? lo0 + tx : lo0, gy = act ? lo1 + ty : lo1;
-    const int cx = wrap(gx, n0), cy = wrap(gy, n1);
-    const size_t c = (size_t)cy * n0 + cx;
+    const int cx = wrap_once(gx, n0), cy = wrap_once(gy, n1);   // a cut axis is longer than its halo
+    const unsigned c = (unsigned)cy * n0 + cx;
     const bool store = act && gx >= a0 && gx < e0 && gy >= a1 && gy < e1;
     // the region ends at an edge of a non-periodic axis
     const bool el0 = ox && lo0 == 0, eh0 = ox && hi0 == n0, el1 = oy && lo1 == 0, eh1 = oy && hi1 == n1;
@@ -92,64 +107,81 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     const bool head = P.kind != 1 ? P.first != 0 : P.group == 0;
     double y1 = 0.0, y2 = 0.0, y0 = 0.0;
     R my = 0;
-    FaceDir<R> dx{0, 0, 0, 0, false}, dy{0, 0, 0, 0, false}, dl{0, 0, 0, 0, false};
     // the extra low face of this thread (edge of a non-periodic axis): faces
     // of the x edge first, then of the y edge
     const int jx = el0 ? h1 : 0, jy = ND == 2 && el1 ? w0 : 0;
     const bool job = tid < jx + jy, jobx = tid < jx;
     int jr = 0, jl = 0, jf = 0;   // slots of its two cells, place of its face
-    if (act) {
-        if (head) {
-            y1 = P.T[c];
-            y0 = y1;
-        } else {
-            y1 = P.in1[c];
-            if (P.kind == 1) {
-                y2 = P.in2[c];
-                y0 = P.Y0c[c];
-                my = ((const R*)P.M)[c];
-            }
+    if (head) {
+        y1 = ld(P.T, c);
+        y0 = y1;
+    } else {
+        y1 = ld(P.in1, c);
+        if (P.kind == 1) {
+            y2 = ld(P.in2, c);
+            y0 = ld((const double*)P.Y0c, c);
+            my = ld((const R*)P.M, c);
         }
-        // beyond an outflow or fixed edge b repeats the edge cell's
-        const size_t cxp = (size_t)cy * n0 + bidx(gx + 1, n0, ox), cyp = (size_t)bidx(gy + 1, n1, oy) * n0 + cx;
-        const R u0 = b0[c], u1 = b1[c], u2 = b2[c];
-        dx = face_dir(u0, u1, u2, b0[cxp], b1[cxp], b2[cxp]);
-        if (ND == 2) dy = face_dir(u1, u0, u2, b1[cyp], b0[cyp], b2[cyp]);
+    }
+    // beyond an outflow or fixed edge b repeats the edge cell's
+    const unsigned cxp = (unsigned)cy * n0 + (ox ? min(gx + 1, n0 - 1) : wrap_once(gx + 1, n0));
+    const unsigned cyp = (unsigned)(oy ? min(gy + 1, n1 - 1) : wrap_once(gy + 1, n1)) * n0 + cx;
+    const R u0 = ld(b0, c), u1 = ld(b1, c), u2 = ld(b2, c);
+    const R x0 = ld(b0, cxp), x1 = ld(b1, cxp), x2 = ld(b2, cxp);
+    R v0 = 0, v1 = 0, v2 = 0, e0b = 0, e1b = 0, e2b = 0;
+    if (ND == 2) {
+        v0 = ld(b0, cyp);
+        v1 = ld(b1, cyp);
+        v2 = ld(b2, cyp);
     }
     if (job) {
         const int q = jobx ? tid : tid - jx;
         jr = jobx ? q * w : q;
         jl = jobx ? (fx ? gxl + q : jr) : (fy ? gyl + q : jr);
         jf = cells + q;
-        const size_t e = jobx ? (size_t)wrap(lo1 + q, n1) * n0 : (size_t)wrap(lo0 + q, n0);
-        const R u0 = b0[e], u1 = b1[e], u2 = b2[e];
-        dl = jobx ? face_dir(u0, u1, u2, u0, u1, u2) : face_dir(u1, u0, u2, u1, u0, u2);
+        const unsigned e = jobx ? (unsigned)wrap_once(lo1 + q, n1) * n0 : (unsigned)wrap_once(lo0 + q, n0);
+        e0b = ld(b0, e);
+        e1b = ld(b1, e);
+        e2b = ld(b2, e);
     }
 
     // dt_par, s and T_ref: the extrema of T, by every workgroup for itself
     if (P.derive) {
         block_state(P.gc, P.src, blockIdx.x == 0, P.state, red, &sst);
-    } else {
-        if (tid == 0) sst = *P.state;
-        __syncthreads();
+        s = __builtin_amdgcn_readfirstlane(sst.s);
+        tref = uniform(sst.tref);
+        cdiv = uniform(sst.cdiv);
     }
-    const int s = __builtin_amdgcn_readfirstlane(sst.s);
-    const double tref = sizeof(R) == 4 ? uniform(sst.tref) : 0.0;
-    const FaceK<R> fk = make_facek<R>(P.gc.kappa0, P.gc.kexp, P.gc.kperp, P.gc.satq, tref);
+    if (sizeof(R) == 8) tref = 0.0;
     int j0 = 1, j1 = 1;
     bool last = true;
     double scale = -P.gc.fac;
     if (P.kind == 1) {
         if (s < P.smin || s > P.s_cap) return;   // uniform over the launch
         const int G = P.groups ? P.groups : (t.nt0 * t.nt1 == 1 ? 1 : max(2, (s + t.f - 1) / t.f));
-        j0 = (int)(((long long)s * P.group + G - 1) / G) + 1;
-        j1 = (int)(((long long)s * (P.group + 1) + G - 1) / G);
+        j0 = (int)(((unsigned)s * P.group + G - 1) / G) + 1;
+        j1 = (int)(((unsigned)s * (P.group + 1) + G - 1) / G);
         last = P.group == G - 1;
-        scale = -uniform(sst.cdiv);
+        scale = -cdiv;
     } else if (P.kind == 2) {
         j1 = P.count;
         last = P.last != 0;
     }
+    // the coefficient rows of up to 64 stages
+    const auto fill_rows = [&](int j) {
+        const int nr = min(64, j1 - j + 1);
+        if (P.coef) {
+            for (int i = tid; i < 5 * nr; i += nt) rows[i] = P.coef[5 * ((size_t)s * (s + 1) / 2 + j) + i];
+        } else if (tid < nr) {
+            rkl2_row(s, j + tid, rows + 5 * tid);
+        }
+    };
+    if (P.kind == 1) fill_rows(j0);
+    const FaceK<R> fk = make_facek<R>(P.gc.kappa0, P.gc.kexp, P.gc.kperp, P.gc.satq, tref);
+    const FaceDir<R> dx = face_dir(u0, u1, u2, x0, x1, x2);
+    FaceDir<R> dy{0, 0, 0, 0, false}, dl{0, 0, 0, 0, false};
+    if (ND == 2) dy = face_dir(u1, u0, u2, v1, v0, v2);
+    if (job) dl = jobx ? face_dir(e0b, e1b, e2b, e0b, e1b, e2b) : face_dir(e1b, e0b, e2b, e1b, e0b, e2b);
 
     const R ih0 = R(P.gc.ih0), ih1 = R(P.gc.ih1);
     const R hih0 = R(0.25 * P.gc.ih0), hih1 = R(0.25 * P.gc.ih1);   // 1/(4h), see cell_slope
@@ -178,14 +210,9 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
 
     double tl = 0.0;
     for (int j = j0; j <= j1; ++j) {
-        if (P.kind == 1 && (j - j0) % 64 == 0) {
+        if (P.kind == 1 && j > j0 && (j - j0) % 64 == 0) {
             __syncthreads();   // the previous rows have been read
-            const int nr = min(64, j1 - j + 1);
-            if (P.coef) {
-                for (int i = tid; i < 5 * nr; i += nt) rows[i] = P.coef[5 * ((size_t)s * (s + 1) / 2 + j) + i];
-            } else if (tid < nr) {
-                rkl2_row(s, j + tid, rows + 5 * tid);
-            }
+            fill_rows(j);
         }
         __syncthreads();
         const R tc = LT[slot];
