@@ -117,10 +117,10 @@ static hipError_t launch_prec(const StageLaunch& P, int nblocks, const Variant& 
 // workgroups.  A chunk of bz planes costs bz + 2 plane iterations (the two
 // before z0 fill the rings); an iteration takes c[k] microseconds with k
 // workgroups on a CU (MC, T^2.5 and saturated flux; measured with 64^3 to
-// 192^3 grids, k = 1, 2, 3; three mixed or two FP64 workgroups fit a CU's
-// registers), and a launch 4 us besides.  Short chunks give a small grid enough
-// workgroups for the 256 CUs, long ones keep the two extra iterations and the
-// halo planes cheap.  The last, partly filled round is priced half by its share
+// 192^3 grids, k = 1, 2, 3; three mixed, two FP64 or three saturated FP64
+// workgroups fit a CU's registers), and a launch 4 us besides.  Short chunks
+// give a small grid enough workgroups for the 256 CUs, long ones keep the two
+// extra iterations and the halo planes cheap.  The last, partly filled round is priced half by its share
 // of the slots and half as a round of its own: workgroups of different rounds
 // overlap, but not fully.
 //
@@ -135,9 +135,11 @@ static hipError_t launch_prec(const StageLaunch& P, int nblocks, const Variant& 
 Variant fit_variant(int precision, Variant v, const GridConst& gc) {
     if (gc.fixed) v = Variant{16, 16, v.bz, 1};   // the tile shape of the ghost-loading kernel
     const bool f32 = precision == RKL_MIXED;
-    const int per_cu = f32 ? 3 : 2;
-    static const double c32[] = {0.0, 1.03, 1.3, 1.6}, c64[] = {0.0, 1.3, 1.95};
-    const double* c = f32 ? c32 : c64;
+    const bool three = !f32 && gc.saturation && gc.kmode != 2 && !gc.fixed && v.bx != 64;   // as three_waves
+    const int per_cu = f32 || three ? 3 : 2;
+    static const double c32[] = {0.0, 1.03, 1.3, 1.6}, c64[] = {0.0, 1.3, 1.95},
+                        c64s[] = {0.0, 1.5, 2.35, 3.15};
+    const double* c = f32 ? c32 : three ? c64s : c64;
     const int64_t tiles = (int64_t)((gc.n0 + v.bx - 1) / v.bx) * ((gc.n1 + v.by - 1) / v.by);
     const int64_t slots = 256 * per_cu;
     int best = v.bz;

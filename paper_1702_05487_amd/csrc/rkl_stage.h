@@ -93,6 +93,15 @@ __device__ __forceinline__ void store_ext(const StageLaunch& P, const TileExt& e
     }
 }
 
+// The saturated FP64 kernels whose registers and LDS let three workgroups share
+// a CU (not those with pow(), 204 VGPRs, nor the 64 x 4 tile's, 56.9 KB) are
+// built for three waves per SIMD, see Prefetch.
+template <typename R, int BX, int BY>
+constexpr bool three_waves(int sat, int km) {
+    return sizeof(R) == 8 && sat != 0 && km != 2 &&
+           3 * sizeof(TileLds<R, (BX + 2) * (BY + 2), (BX + 1) * BY, BX*(BY + 1)>) <= 156 * 1024;
+}
+
 // MODE 1: 3-D grid, tile shape fixed at compile time (run_tile's CBX, CBY);
 // MODE 0: runtime tile shape; MODE 2: runtime tile shape with the ghost
 // layers of fixed axes
@@ -118,8 +127,10 @@ __global__ __launch_bounds__(BX* BY) void stage_kernel(StageLaunch P) {
     if (!stage_args(P, MODE == 1, P.state->s, P.state->cdiv, a)) return;
     const FaceK<R> fk = make_facek<R>(P.kappa0, P.kexp, P.kperp, P.satq, tref);
     if constexpr (MODE == 1) {
+        using PF = typename std::conditional<three_waves<R, BX, BY>(SAT, KM), Prefetch<1, 1, 0, true>,
+                                             Prefetch<2, 2, 2, false>>::type;
         const TileExt e =
-            run_tile<R, LIM, SAT, KM, PL, (BX + 1) * BY, BX*(BY + 1), BX, BY, false, 6, true>(a, fk, tref, L);
+            run_tile<R, LIM, SAT, KM, PL, (BX + 1) * BY, BX*(BY + 1), BX, BY, false, 6, true, PF>(a, fk, tref, L);
         if (a.ext) store_ext<BX * BY>(P, e);   // uniform: the last stage of a routed sequence
     } else if constexpr (MODE == 2)
         run_tile<R, LIM, SAT, KM, PL, (BX + 1) * BY, BX*(BY + 1), 0, 0, true>(a, fk, tref, L);

@@ -338,6 +338,22 @@ __device__ __forceinline__ double stage_combine(double mu, double nu, double omn
     return fma(gt, my0, fma(mut, tl, fma(omn, y0, fma(nu, ym2, mu * ym1))));
 }
 
+// What the unrolled loop keeps in registers: T, b and the pointwise inputs are
+// loaded TD, BD and PD planes ahead, and with LR the own cell's slopes and unit
+// vector are read back from LDS.  Two planes ahead of everything is the fastest
+// where the registers allow as many waves either way (mixed, three of 158 VGPRs;
+// FP64, two of 209): one plane ahead frees a fourth mixed wave and still takes
+// 14 % more (512^3 1335 -> 1520 us a stage).  The saturated FP64 kernels, with a
+// root and a reciprocal more per face, gain from a third wave (150 VGPRs; 512^3
+// 2222 -> 2162 us, 384^3 965 -> 934 us), the classical ones do not (256^3 275 ->
+// 295 us).  The clock takes most of that gain: 2.06 GHz at two FP64 waves, 1.92
+// at three.
+template <int TD_, int BD_, int PD_, bool LR_>
+struct Prefetch {
+    static constexpr int TD = TD_, BD = BD_, PD = PD_;
+    static constexpr bool LR = LR_;
+};
+
 // CBX, CBY > 0: the tile shape is a compile-time constant, the grid is 3-D
 // and the workgroup has exactly CBX*CBY threads (one cell each); the tile
 // strides are then constants and the face code has no runtime branches.
@@ -348,7 +364,7 @@ __device__ __forceinline__ double stage_combine(double mu, double nu, double omn
 // lines that neighbouring tiles share (temperatures, unit vectors) stay.
 // Neither changes a value.
 template <typename R, bool LIM, int SAT, int KM, int PLMAX, int FXMAX, int FYMAX, int CBX = 0, int CBY = 0,
-          bool GH = false, int UNR = 1, bool NT = false>
+          bool GH = false, int UNR = 1, bool NT = false, typename PF = Prefetch<2, 2, 2, false>>
 __device__ __forceinline__ TileExt run_tile(const TileArgs& a, const FaceK<R>& fk, double tref,
                                             TileLds<R, PLMAX, FXMAX, FYMAX>& L) {
     constexpr bool FIX = CBX > 0;
@@ -439,70 +455,63 @@ __device__ __forceinline__ TileExt run_tile(const TileArgs& a, const FaceK<R>& f
         // of a ring of length L, P = (k - z0 + 2) mod 6.  The loop is unrolled
         // six-fold (every L divides six) with P a compile-time constant, so each
         // value stays in one register from its load to its last use and no
-        // plane-to-plane moves are left.  Loads are two planes ahead, and values
-        // stay in their loaded type until they are used, so that no conversion
-        // forces an early wait.
-        constexpr int LT = 6;          // own FP64 input: planes k .. k+4
-        constexpr int LB = 6;          // own unit vector: planes k .. k+3
-        double tq[LT];                 // own input Y_{j-1}, FP64
+        // plane-to-plane moves are left.  T(k+2+TD), b(k+1+BD) and the pointwise
+        // inputs of plane k+PD are loaded at plane k, into slots whose values have
+        // been used, and stay in their loaded type until they are used, so that no
+        // conversion forces an early wait.
+        constexpr int TD = PF::TD, BD = PF::BD, PD = PF::PD;
+        constexpr bool LR = PF::LR;
+        constexpr int LH = TD, LD = BD, LB = LR ? BD : (BD == 1 ? 3 : 6), LP = PD + 1;   // ring lengths
+        double tq[6];                  // own input Y_{j-1}, FP64
         R oq[3];                       // the same in flux precision: planes k .. k+2
-        double th[2];                  // halo cell input, FP64: planes k+2, k+3 (k+4 loaded into the slot of k+2)
+        double th[LH];                 // halo cell input, FP64
         R hq[3];                       // halo cell input in flux precision: planes k .. k+2
         R ob[LB][3];                   // own unit vector
-        R pbd[2][3];                   // halo unit vector: planes k+1, k+2 (k+3 loaded into the slot of k+1)
-        R os[2][3];                    // own slopes: planes k, k+1
+        R pbd[LD][3];                  // halo unit vector
+        R os[2][3];                    // own slopes: planes k, k+1 (not LR)
         R zf[2];                       // +z face flux: planes k-1, k
-        double qym2[3], qy0[3];        // pointwise stage inputs Y_{j-2}, Y0: planes k .. k+2
-        R qmy0[3];                     // tau M(Y0): planes k .. k+2
-        for (int r = 0; r < LT; ++r) tq[r] = 0.0;
+        double qym2[LP], qy0[LP];       // pointwise stage inputs Y_{j-2}, Y0
+        R qmy0[LP];                    // tau M(Y0)
+        for (int r = 0; r < 6; ++r) tq[r] = 0.0;
+        for (int r = 0; r < 3; ++r) oq[r] = hq[r] = 0;
+        for (int r = 0; r < 2; ++r) zf[r] = os[r][0] = os[r][1] = os[r][2] = 0;
+        for (int r = 0; r < LH; ++r) th[r] = 0.0;
         for (int r = 0; r < LB; ++r) ob[r][0] = ob[r][1] = ob[r][2] = 0;
-        for (int r = 0; r < 3; ++r) {
-            oq[r] = hq[r] = 0;
+        for (int r = 0; r < LD; ++r) pbd[r][0] = pbd[r][1] = pbd[r][2] = 0;
+        for (int r = 0; r < LP; ++r) {
             qym2[r] = qy0[r] = 0.0;
             qmy0[r] = 0;
         }
-        for (int r = 0; r < 2; ++r) {
-            th[r] = 0.0;
-            zf[r] = 0;
-            pbd[r][0] = pbd[r][1] = pbd[r][2] = 0;
-            os[r][0] = os[r][1] = os[r][2] = 0;
-        }
         const bool pw = own && a.kind == 2;
+        int pzt = bidx(z0 + TD, n2, oz), pzb = bidx(z0 - 1 + BD, n2, oz);   // planes k+2+TD and k+1+BD
+        const auto next = [&](int p, int m) { return oz ? min(max(m, 0), n2 - 1) : (p + 1 == n2 ? 0 : p + 1); };
 
-        // prologue (P = 0 at k = z0 - 2): T(z0-2 .. z0+1), b(z0-1), b(z0)
-        {
-            const double* p0 = a.Yin + (size_t)bidx(z0 - 2, n2, oz) * plane;
-            const double* p1 = a.Yin + (size_t)bidx(z0 - 1, n2, oz) * plane;
-            const double* p2 = a.Yin + (size_t)bidx(z0, n2, oz) * plane;
-            const double* p3 = a.Yin + (size_t)bidx(z0 + 1, n2, oz) * plane;
-            const size_t pb0 = (size_t)bidx(z0 - 1, n2, oz) * plane;
-            const size_t pb1 = (size_t)bidx(z0, n2, oz) * plane;
-            if (own) {
-                tq[0] = tld(p0, z0 - 2, oxy, gco);
-                tq[1] = tld(p1, z0 - 1, oxy, gco);
-                tq[2] = tld(p2, z0, oxy, gco);
-                tq[3] = tld(p3, z0 + 1, oxy, gco);
-                ob[1][0] = b0[pb0 + oxy]; ob[1][1] = b1[pb0 + oxy]; ob[1][2] = b2[pb0 + oxy];
-                ob[2][0] = b0[pb1 + oxy]; ob[2][1] = b1[pb1 + oxy]; ob[2][2] = b2[pb1 + oxy];
-            }
+        // prologue (P = 0 at k = z0 - 2): T(k .. k+1+TD), b(k+1 .. k+BD)
+#pragma unroll
+        for (int m = 0; m < 2 + TD; ++m) {
+            const double* p = a.Yin + (size_t)bidx(z0 - 2 + m, n2, oz) * plane;
+            if (own) tq[m] = tld(p, z0 - 2 + m, oxy, gco);
             if (hjob) {
-                const double h1 = tld(p0, z0 - 2, hxy, gch), h2 = tld(p1, z0 - 1, hxy, gch);
-                th[0] = tld(p2, z0, hxy, gch);
-                th[1] = tld(p3, z0 + 1, hxy, gch);
-                hq[0] = to_r<R>(h1, tref);
-                hq[1] = to_r<R>(h2, tref);
-                L.T[0][hslot] = hq[0];
-                L.T[1][hslot] = hq[1];
+                const double v = tld(p, z0 - 2 + m, hxy, gch);
+                if (m < 2) {
+                    hq[m] = to_r<R>(v, tref);
+                    L.T[m][hslot] = hq[m];
+                } else {
+                    th[(m - 2) % LH] = v;
+                }
             }
-            if (djob) {
-                pbd[1][0] = b0[pb0 + hxy]; pbd[1][1] = b1[pb0 + hxy]; pbd[1][2] = b2[pb0 + hxy];
-                pbd[0][0] = b0[pb1 + hxy]; pbd[0][1] = b1[pb1 + hxy]; pbd[0][2] = b2[pb1 + hxy];
-            }
+        }
+#pragma unroll
+        for (int m = 1; m <= BD; ++m) {
+            const size_t pb = (size_t)bidx(z0 - 2 + m, n2, oz) * plane;
+            if (own) { ob[m % LB][0] = b0[pb + oxy]; ob[m % LB][1] = b1[pb + oxy]; ob[m % LB][2] = b2[pb + oxy]; }
+            if (djob) { pbd[m % LD][0] = b0[pb + hxy]; pbd[m % LD][1] = b1[pb + hxy]; pbd[m % LD][2] = b2[pb + hxy]; }
+        }
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
             if (own) {
-                oq[0] = to_r<R>(tq[0], tref);
-                oq[1] = to_r<R>(tq[1], tref);
-                L.T[0][oslot] = oq[0];
-                L.T[1][oslot] = oq[1];
+                oq[m] = to_r<R>(tq[m], tref);
+                L.T[m][oslot] = oq[m];
             }
         }
         __syncthreads();
@@ -514,84 +523,93 @@ __device__ __forceinline__ TileExt run_tile(const TileArgs& a, const FaceK<R>& f
             constexpr int P = decltype(ph)::value;
             constexpr int r0 = P % 3, r1 = (P + 1) % 3, r2 = (P + 2) % 3;   // 3-rings: planes k, k+1, k+2
             constexpr int d0 = P % 2, d1 = (P + 1) % 2;                     // 2-rings: planes k, k+1
-            constexpr int t0 = r0, t1 = r1, t2 = r2, e0 = d0, e1 = d1;
             // ---- A: T(k+2) into the ring, b(k+1) into the b ring
             if (own) {
-                oq[r2] = to_r<R>(tq[(P + 2) % LT], tref);
-                L.T[t2][oslot] = oq[r2];
+                oq[r2] = to_r<R>(tq[(P + 2) % 6], tref);
+                L.T[r2][oslot] = oq[r2];
                 const R* bn = ob[(P + 1) % LB];
-                L.B[e0][0][oslot] = bn[0]; L.B[e0][1][oslot] = bn[1]; L.B[e0][2][oslot] = bn[2];
+                L.B[d0][0][oslot] = bn[0]; L.B[d0][1][oslot] = bn[1]; L.B[d0][2][oslot] = bn[2];
             }
             if (hjob) {
-                hq[r2] = to_r<R>(th[d0], tref);
-                L.T[t2][hslot] = hq[r2];
+                hq[r2] = to_r<R>(th[P % LH], tref);
+                L.T[r2][hslot] = hq[r2];
             }
-            if (djob) { L.B[e0][0][hslot] = pbd[d1][0]; L.B[e0][1][hslot] = pbd[d1][1]; L.B[e0][2][hslot] = pbd[d1][2]; }
-            // prefetch two planes ahead: T(k+4) and b(k+3), used at plane k+2
-            if (k + 2 < z1) {
-                const double* pt = a.Yin + (size_t)pz4 * plane;
-                const int pbz = oz ? min(k + 3, n2 - 1) : (pz4 == 0 ? n2 - 1 : pz4 - 1);
-                const size_t pb = (size_t)pbz * plane;
+            if (djob) {
+                const R* bn = pbd[(P + 1) % LD];
+                L.B[d0][0][hslot] = bn[0]; L.B[d0][1][hslot] = bn[1]; L.B[d0][2][hslot] = bn[2];
+            }
+            // prefetch
+            if (k + TD < z1) {
+                const double* pt = a.Yin + (size_t)pzt * plane;
+                if (own) tq[(P + 2 + TD) % 6] = tld(pt, k + 2 + TD, oxy, gco);
+                if (hjob) th[P % LH] = tld(pt, k + 2 + TD, hxy, gch);
+                pzt = next(pzt, k + 3 + TD);
+            }
+            if (k + BD < z1) {
+                const size_t pb = (size_t)pzb * plane;
                 if (own) {
-                    tq[(P + 4) % LT] = tld(pt, k + 4, oxy, gco);
-                    R* bl = ob[(P + 3) % LB];
+                    R* bl = ob[(P + 1 + BD) % LB];
                     bl[0] = b0[pb + oxy]; bl[1] = b1[pb + oxy]; bl[2] = b2[pb + oxy];
                 }
-                if (hjob) th[d0] = tld(pt, k + 4, hxy, gch);
-                if (djob) { pbd[d1][0] = b0[pb + hxy]; pbd[d1][1] = b1[pb + hxy]; pbd[d1][2] = b2[pb + hxy]; }
-                pz4 = oz ? min(k + 5, n2 - 1) : (pz4 + 1 == n2 ? 0 : pz4 + 1);
+                if (djob) {
+                    R* bl = pbd[(P + 1 + BD) % LD];
+                    bl[0] = b0[pb + hxy]; bl[1] = b1[pb + hxy]; bl[2] = b2[pb + hxy];
+                }
+                pzb = next(pzb, k + 2 + BD);
             }
-            if (pw && k + 2 >= z0 && k + 2 < z1) {
+            if (pw && k + PD >= z0 && k + PD < z1) {
                 // read once and not again in this launch: streamed past the caches (NT)
-                const size_t o = (size_t)(k + 2) * plane + oxy;
+                const size_t o = (size_t)(k + PD) * plane + oxy;
+                constexpr int q = (P + PD) % LP;
                 if constexpr (NT) {
-                    qym2[r2] = __builtin_nontemporal_load(a.Ym2 + o);
-                    qy0[r2] = __builtin_nontemporal_load(a.Y0 + o);
-                    qmy0[r2] = __builtin_nontemporal_load((const R*)a.MY0in + o);
+                    qym2[q] = __builtin_nontemporal_load(a.Ym2 + o);
+                    qy0[q] = __builtin_nontemporal_load(a.Y0 + o);
+                    qmy0[q] = __builtin_nontemporal_load((const R*)a.MY0in + o);
                 } else {
-                    qym2[r2] = a.Ym2[o];
-                    qy0[r2] = a.Y0[o];
-                    qmy0[r2] = ((const R*)a.MY0in)[o];
+                    qym2[q] = a.Ym2[o];
+                    qy0[q] = a.Y0[o];
+                    qmy0[q] = ((const R*)a.MY0in)[o];
                 }
             }
 
             // ---- B: slopes of plane k+1.  In-plane neighbours of T(k+1) come from
             // the ring (written one plane earlier); z neighbours from registers.
             if (own) {
-                const R* T1 = L.T[t1];
-                const R s0 = cell_slope<R, LIM>(T1[oslot - 1], oq[r1], T1[oslot + 1], hih0);
-                const R s1 = cell_slope<R, LIM>(T1[oslot - px], oq[r1], T1[oslot + px], hih1);
-                const R s2 = cell_slope<R, LIM>(oq[r0], oq[r1], oq[r2], hih2);
-                L.S[e0][0][oslot] = s0; L.S[e0][1][oslot] = s1; L.S[e0][2][oslot] = s2;
-                os[d1][0] = s0; os[d1][1] = s1; os[d1][2] = s2;
+                const R* T1 = L.T[r1];
+                os[d1][0] = cell_slope<R, LIM>(T1[oslot - 1], oq[r1], T1[oslot + 1], hih0);
+                os[d1][1] = cell_slope<R, LIM>(T1[oslot - px], oq[r1], T1[oslot + px], hih1);
+                os[d1][2] = cell_slope<R, LIM>(oq[r0], oq[r1], oq[r2], hih2);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) L.S[d0][d][oslot] = os[d1][d];
             }
             if (djob) {
-                const R* T1 = L.T[t1];
-                if (dxh) L.S[e0][1][hslot] = cell_slope<R, LIM>(T1[hslot - px], hq[r1], T1[hslot + px], hih1);
-                else     L.S[e0][0][hslot] = cell_slope<R, LIM>(T1[hslot - 1], hq[r1], T1[hslot + 1], hih0);
-                L.S[e0][2][hslot] = cell_slope<R, LIM>(hq[r0], hq[r1], hq[r2], hih2);
+                const R* T1 = L.T[r1];
+                if (dxh) L.S[d0][1][hslot] = cell_slope<R, LIM>(T1[hslot - px], hq[r1], T1[hslot + px], hih1);
+                else     L.S[d0][0][hslot] = cell_slope<R, LIM>(T1[hslot - 1], hq[r1], T1[hslot + 1], hih0);
+                L.S[d0][2][hslot] = cell_slope<R, LIM>(hq[r0], hq[r1], hq[r2], hih2);
             }
 
-            // ---- C: faces of plane k (inputs written in earlier planes; the low
-            // side of the own faces from registers)
-            const R* ob0 = ob[P % LB];         // b(k)
-            const R* ob1 = ob[(P + 1) % LB];   // b(k+1)
+            // ---- C: faces of plane k (inputs written in earlier planes; the low side
+            // of the own faces from registers, or with LR its slopes and unit vector
+            // back from LDS, which saves 12 values per thread)
+            const R* Tk = L.T[r0];
+            const R(*S)[PLMAX] = L.S[d1];
+            const R(*Bv)[PLMAX] = L.B[d1];
+            const auto so = [&](int d) { return LR ? S[d][oslot] : os[d0][d]; };
+            const auto bo = [&](int d) { return LR ? Bv[d][oslot] : ob[P % LB][d]; };
             if (k >= z0) {
-                const R* Tk = L.T[t0];
-                const R(*S)[PLMAX] = L.S[e1];
-                const R(*Bv)[PLMAX] = L.B[e1];
-                R* FX = L.FX[e0];
-                R* FY = L.FY[e0];
+                R* FX = L.FX[d0];
+                R* FY = L.FY[d0];
                 if (own) {
                     const int r = oslot + 1;
                     FX[ty * (bx + 1) + tx + 1] = face_flux<R, LIM, SAT, KM>(
-                        oq[r0], Tk[r], ih0, os[d0][1], S[1][r], os[d0][2], S[2][r],
-                        ob0[0], ob0[1], ob0[2], Bv[0][r], Bv[1][r], Bv[2][r], fk);
+                        oq[r0], Tk[r], ih0, so(1), S[1][r], so(2), S[2][r],
+                        bo(0), bo(1), bo(2), Bv[0][r], Bv[1][r], Bv[2][r], fk);
                     if (do_y) {
                         const int u = oslot + px;
                         FY[(ty + 1) * bx + tx] = face_flux<R, LIM, SAT, KM>(
-                            oq[r0], Tk[u], ih1, os[d0][0], S[0][u], os[d0][2], S[2][u],
-                            ob0[1], ob0[0], ob0[2], Bv[1][u], Bv[0][u], Bv[2][u], fk);
+                            oq[r0], Tk[u], ih1, so(0), S[0][u], so(2), S[2][u],
+                            bo(1), bo(0), bo(2), Bv[1][u], Bv[0][u], Bv[2][u], fk);
                     }
                 }
                 if (fjob) {
@@ -605,22 +623,24 @@ __device__ __forceinline__ TileExt run_tile(const TileArgs& a, const FaceK<R>& f
             }
             zf[d0] = 0;
             if (do_z && own && k >= z0 - 1) {
-                zf[d0] = face_flux<R, LIM, SAT, KM>(oq[r0], oq[r1], ih2, os[d0][0], os[d1][0], os[d0][1], os[d1][1],
-                                                    ob0[2], ob0[0], ob0[1], ob1[2], ob1[0], ob1[1], fk);
+                const R(*B1)[PLMAX] = L.B[d0];
+                const auto b1k = [&](int d) { return LR ? B1[d][oslot] : ob[(P + 1) % LB][d]; };   // b(k+1)
+                zf[d0] = face_flux<R, LIM, SAT, KM>(oq[r0], oq[r1], ih2, so(0), os[d1][0], so(1), os[d1][1],
+                                                    bo(2), bo(0), bo(1), b1k(2), b1k(0), b1k(1), fk);
             }
             __syncthreads();
 
             // ---- D: divergence and the stage update of plane k
             if (k >= z0 && store) {
-                const R* FX = L.FX[e0];
-                const R* FY = L.FY[e0];
+                const R* FX = L.FX[d0];
+                const R* FY = L.FY[d0];
                 const int fx = ty * (bx + 1) + tx;
                 R div = (FX[fx + 1] - FX[fx]) * ih0;
                 if (do_y) div = fma(FY[(ty + 1) * bx + tx] - FY[ty * bx + tx], ih1, div);
                 if (do_z) div = fma(zf[d0] - zf[d1], ih2, div);
                 const size_t o = (size_t)k * plane + oxy;
                 const double tl = a.scale * (double)div;
-                const double yk = tq[P % LT];
+                const double yk = tq[P % 6];
                 if (a.kind == 0) {
                     a.Yout[o] = tl;
                 } else if (a.kind == 1) {
@@ -630,8 +650,8 @@ __device__ __forceinline__ TileExt run_tile(const TileArgs& a, const FaceK<R>& f
                 } else if (a.kind == 3) {
                     a.Yout[o] = yk + tl;
                 } else {
-                    const double y = stage_combine(a.mu, a.nu, a.omn, a.mut, a.gt, yk, qym2[r0], qy0[r0], tl,
-                                                   (double)qmy0[r0]);
+                    const double y = stage_combine(a.mu, a.nu, a.omn, a.mut, a.gt, yk, qym2[P % LP], qy0[P % LP], tl,
+                                                   (double)qmy0[P % LP]);
                     if constexpr (NT) __builtin_nontemporal_store(y, a.Yout + o);
                     else a.Yout[o] = y;
                     if (ext_on) {

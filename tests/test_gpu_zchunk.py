@@ -91,3 +91,38 @@ def test_marched_ragged(edges, lim, sat, law, precision):
         plan.superstep(Td, bd, dt)
     assert torch.equal(Td, many)
     plan.close()
+
+
+@pytest.mark.parametrize("edges,lim,sat,law", [
+    ((0, 0, 0), 1, 1, 2.5), ((1, 0, 1), 0, 2, 2.5), ((0, 1, 1), 1, 1, 0.0), ((1, 1, 0), 0, 1, 1.7),
+])
+@pytest.mark.parametrize("depth", (1, 2, 5, 7, 13))
+def test_three_waves(depth, edges, lim, sat, law):
+    """The saturated FP64 kernel reads the own cell back from LDS and loads one
+    plane ahead on the 32 x 8 and 16 x 16 tiles; the 64 x 4 tile (variants 2, 3
+    and 7) keeps it in registers and loads two ahead: the same bits on ragged
+    sides, and the oracle's values.  512 tiles, so that every depth marches."""
+    import torch
+    from paper_1702_05487_amd import rkl
+    print("three waves", depth, edges, lim, sat, law, flush=True)
+    n = (500, 251, depth)
+    rng = np.random.default_rng(50 + depth)
+    T = 1.0 + 0.2 * rng.random(n[::-1])
+    b = inputs.unit_vectors(rng.standard_normal((3,) + n[::-1]))
+    p = dict(inputs.BASE, limiter=lim, saturation=sat, phi=0.01, kappa_exp=law, kperp_ratio=0.02, boundary=edges)
+    g = oracle_grid(n, H, 3, p)
+    dt = inputs.midpoint_ratio(4) * oracle.dt_par(g, T)
+    bd = torch.from_numpy(b).to("cuda:0")
+    got = []
+    for v in range(8):
+        plan = rkl.Plan([lib_desc(n, H, 3, p)], precision="fp64", variant=v)
+        Td = torch.from_numpy(T).to("cuda:0")
+        assert plan.superstep(Td, bd, dt) == 4
+        plan.close()
+        got.append(Td.cpu().numpy())
+        assert np.array_equal(got[v], got[0]), v
+    oracle.set_threads(16)
+    ref, s, _ = oracle.superstep(g, T, b, dt)
+    oracle.set_threads(1)
+    assert s == 4
+    assert rel_l1(got[0], ref) <= 1e-12
