@@ -205,6 +205,14 @@ hipError_t launch_stage(int precision, Variant v, const GridConst& gc, int kind,
     a.scale = 0.0;
     a.mu = a.nu = a.omn = a.mut = a.gt = 0.0;
     a.ext = 0;
+    // A grid whose stage fields (48 B a cell) about fit the 256 MB last-level
+    // cache finds its pointwise fields there again in the next stage; larger ones
+    // stream them past it, since they only displace the halo lines that tiles
+    // share.  Mixed, us a stage, streamed / kept: 128^3 26.2 / 25.3, 150 x 127 x
+    // 101 29.6 / 27.4, 160^3 43.8 / 40.6, 192^3 (340 MB) 64.3 / 62.1; 200^3 (384 MB)
+    // 84.0 / 84.6, 208^3 81 / 88, 256^3 164 / 171.  In FP64 (64 B) 128^3 34.8 / 33.7
+    // and 160^3 58.9 / 57.1, but 176^3 (349 MB) no longer: not built.
+    P.cached = precision == RKL_MIXED && 48 * (int64_t)gc.n0 * gc.n1 * gc.n2 <= (int64_t)352 << 20;
     P.ntx = (gc.n0 + v.bx - 1) / v.bx;
     P.nty = (gc.n1 + v.by - 1) / v.by;
     P.bz = v.bz;

@@ -21,6 +21,7 @@ struct StageLaunch {
     double sub_scale;    // kind 3: -tau_sub (gamma-1)/rho
     Route route;         // route.A != NULL: Yin, Ym2, Yout chosen on the device (kinds 1, 2)
     ExtOut ext;          // ext.part != NULL: the launch of stage j = s keeps the extrema of Y_s
+    bool cached;         // the stage's fields about fit the last-level cache (stage_kernel MODE 3)
 };
 
 // The buffers a routed stage reads, which follow from j alone, so that loads
@@ -104,7 +105,8 @@ constexpr bool three_waves(int sat, int km) {
 
 // MODE 1: 3-D grid, tile shape fixed at compile time (run_tile's CBX, CBY);
 // MODE 0: runtime tile shape; MODE 2: runtime tile shape with the ghost
-// layers of fixed axes
+// layers of fixed axes; MODE 3: MODE 1 with the pointwise fields kept in the
+// caches (run_tile's NT)
 template <typename R, bool LIM, int SAT, int KM, int BX, int BY, int MODE>
 __global__ __launch_bounds__(BX* BY) void stage_kernel(StageLaunch P) {
     constexpr int PL = (BX + 2) * (BY + 2);
@@ -124,13 +126,14 @@ __global__ __launch_bounds__(BX* BY) void stage_kernel(StageLaunch P) {
     a.z1 = min(a.z0 + P.bz, a.n2);
     stage_inputs(P, a);
     const double tref = sizeof(R) == 4 ? P.state->tref : 0.0;
-    if (!stage_args(P, MODE == 1, P.state->s, P.state->cdiv, a)) return;
+    constexpr bool FIX = MODE == 1 || MODE == 3;
+    if (!stage_args(P, FIX, P.state->s, P.state->cdiv, a)) return;
     const FaceK<R> fk = make_facek<R>(P.kappa0, P.kexp, P.kperp, P.satq, tref);
-    if constexpr (MODE == 1) {
+    if constexpr (FIX) {
         using PF = typename std::conditional<three_waves<R, BX, BY>(SAT, KM), Prefetch<1, 1, 0, true>,
                                              Prefetch<2, 2, 2, false>>::type;
         const TileExt e =
-            run_tile<R, LIM, SAT, KM, PL, (BX + 1) * BY, BX*(BY + 1), BX, BY, false, 6, true, PF>(a, fk, tref, L);
+            run_tile<R, LIM, SAT, KM, PL, (BX + 1) * BY, BX*(BY + 1), BX, BY, false, 6, MODE == 1, PF>(a, fk, tref, L);
         if (a.ext) store_ext<BX * BY>(P, e);   // uniform: the last stage of a routed sequence
     } else if constexpr (MODE == 2)
         run_tile<R, LIM, SAT, KM, PL, (BX + 1) * BY, BX*(BY + 1), 0, 0, true>(a, fk, tref, L);
@@ -166,6 +169,8 @@ static hipError_t launch_law(const StageLaunch& P, int nblocks, bool lim, int sa
 // the rkl_stage_*.hip units, which compile in parallel.
 template <typename R, int BX, int BY>
 hipError_t launch_shape(const StageLaunch& P, int nblocks, bool lim, int sat, hipStream_t st) {
+    if constexpr (sizeof(R) == 4)
+        if (P.t.ndim == 3 && P.cached) return launch_law<R, BX, BY, 3>(P, nblocks, lim, sat, st);
     if (P.t.ndim == 3) return launch_law<R, BX, BY, 1>(P, nblocks, lim, sat, st);
     return launch_law<R, BX, BY, 0>(P, nblocks, lim, sat, st);
 }

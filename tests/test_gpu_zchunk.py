@@ -126,3 +126,29 @@ def test_three_waves(depth, edges, lim, sat, law):
     oracle.set_threads(1)
     assert s == 4
     assert rel_l1(got[0], ref) <= 1e-12
+
+
+@pytest.mark.parametrize("depth", (171, 172))
+def test_cached_and_streamed(depth):
+    """Mixed grids up to 352 MiB of stage fields keep the pointwise fields in
+    the caches, larger ones stream them past: 172 planes of 212 x 212 cells are
+    the first beyond.  Both, and all one-stage variants, have the fused
+    kernel's bits."""
+    import torch
+    from paper_1702_05487_amd import rkl
+    print("cached", depth, flush=True)
+    n = (212, 212, depth)
+    assert (48 * n[0] * n[1] * n[2] <= 352 << 20) == (depth == 171)
+    rng = np.random.default_rng(9)
+    T = 1.0 + 0.2 * rng.random(n[::-1])
+    b = torch.from_numpy(inputs.unit_vectors(rng.standard_normal((3,) + n[::-1]))).to("cuda:0", torch.float32)
+    p = dict(inputs.SPITZER_MC_SAT, phi=0.003)
+    dt = inputs.midpoint_ratio(5) * oracle.dt_par(oracle_grid(n, H, 3, p), T)
+    got = []
+    for v in (8, 0, 2, 4, 6):
+        plan = rkl.Plan([lib_desc(n, H, 3, p)], precision="mixed", variant=v)
+        Td = torch.from_numpy(T).to("cuda:0")
+        assert plan.superstep(Td, b, dt) == 5
+        plan.close()
+        got.append(Td)
+        assert torch.equal(Td, got[0]), v
