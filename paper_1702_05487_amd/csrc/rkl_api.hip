@@ -589,7 +589,18 @@ static rkl_status extrema_source(rkl_plan_t p, int32_t g, const double* T, doubl
 // wait_host after everything that may run meanwhile has been enqueued: it
 // polls the pinned words (the stream is not drained), looking at the stream
 // now and then so that a failed launch ends the wait.  Waits for both words,
-// so that no store is left for a later call.
+// so that no store is left for a later call.  A call that fails anywhere after
+// arm_host drains its stream before it returns (Drain): the launch that stores
+// the words may be pending, and its stores would reach the next call; so may
+// launches that read the caller's fields.
+struct Drain {
+    hipStream_t st;
+    bool on = true;
+    ~Drain() {
+        if (on) (void)hipStreamSynchronize(st);
+    }
+};
+
 static rkl_status arm_host(rkl_plan_t p, hipStream_t st) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     HIPCHECK(hipStreamIsCapturing(st, &cs), "capture query");
@@ -702,6 +713,7 @@ rkl_status rkl_flux_div(rkl_plan_t p, int32_t g, const double* T, const void* b,
 static rkl_status read_dt_par(rkl_plan_t p, int32_t g, const double* T, double* dtp, hipStream_t s) {
     rkl_status st = arm_host(p, s);
     if (st != RKL_OK) return st;
+    Drain undo{s};
     StateSource q;
     if ((st = extrema_source(p, g, T, 0.0, 1, p->smax, 1024, 1024, &q, s)) != RKL_OK) return st;
     q.host = p->host;
@@ -709,6 +721,7 @@ static rkl_status read_dt_par(rkl_plan_t p, int32_t g, const double* T, double* 
     HostWords w;
     if ((st = wait_host(p, s, &w)) != RKL_OK) return st;
     *dtp = w.dt_par;
+    undo.on = false;
     return RKL_OK;
 }
 
@@ -729,6 +742,7 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
     if (!(dt_hyp >= 0.0) || !std::isfinite(dt_hyp)) return fail(RKL_EINVAL, "dt_hyp must be finite and >= 0");
     hipStream_t s = (hipStream_t)stream;
     if ((st = arm_host(p, s)) != RKL_OK) return st;
+    Drain undo{s};
     const GridConst& gc = p->gc[g];
     const Variant v = variant_get(p->variant), v1 = fitted(p, g);
     const size_t rs = p->precision == RKL_MIXED ? sizeof(float) : sizeof(double);
@@ -766,6 +780,7 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
         P.groups = flat_groups(P.t, S);
         for (int k = 1; k < P.groups; ++k)
             if ((st = flat_group(p, g, P, k, s)) != RKL_OK) return st;
+        undo.on = false;
         return RKL_OK;
     }
 
@@ -829,6 +844,7 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
     }
     if (S == 1)   // RKL1 with one stage: Y1 was written next to T (stage 1 reads T around each cell)
         HIPCHECK(hipMemcpyAsync(T, bufs[0], sizeof(double) * n, hipMemcpyDeviceToDevice, s), "result copy");
+    undo.on = false;
     return RKL_OK;
 }
 
