@@ -87,7 +87,12 @@ struct HostWords {
 constexpr double kNoDtPar = -1.0;
 constexpr int32_t kNoStages = -0x7fffffff - 1;
 
-__device__ inline void store_host(HostWords* h, const GridState& o) {
+// The calls that read dt_par (mode 1) may return as soon as they see the words,
+// with nothing enqueued behind: whatever the launch stores besides is stored
+// before them, and visible to any stream (`last`).  A super-step has stages
+// enqueued on its stream by then, so its words go out first.
+__device__ inline void store_host(HostWords* h, const GridState& o, bool last) {
+    if (last) __threadfence_system();
     __hip_atomic_store(&h->dt_par, o.dt_par, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&h->s, o.s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -202,9 +207,10 @@ __device__ __forceinline__ void block_state(const GridConst& g, const StateSourc
         if (tid == 0) {
             *out = o;
             if (write) {
-                if (q.host) store_host(q.host, o);   // first: the host is waiting
+                if (q.host && q.mode == 0) store_host(q.host, o, false);
                 *state = o;
                 if (q.s_out) *q.s_out = o.s;
+                if (q.host && q.mode != 0) store_host(q.host, o, true);
             }
         }
     }
