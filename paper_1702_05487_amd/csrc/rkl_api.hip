@@ -3,6 +3,7 @@
 // sequences of the single-grid entry points.
 #include <cmath>
 #include <cstdio>
+#include <sched.h>
 #include <cstring>
 #include <functional>
 #include <string>
@@ -588,7 +589,9 @@ static rkl_status extrema_source(rkl_plan_t p, int32_t g, const double* T, doubl
 // Read-back of dt_par and s.  arm_host before the launch that stores them,
 // wait_host after everything that may run meanwhile has been enqueued: it
 // polls the pinned words (the stream is not drained), looking at the stream
-// now and then so that a failed launch ends the wait.  Waits for both words,
+// now and then so that a failed launch ends the wait.  A process that set
+// hipDeviceScheduleBlockingSync sleeps in hipStreamSynchronize after the first
+// 4096 looks instead of spinning on.  Waits for both words,
 // so that no store is left for a later call.  A call that fails anywhere after
 // arm_host drains its stream before it returns (Drain): the launch that stores
 // the words may be pending, and its stores would reach the next call; so may
@@ -623,6 +626,12 @@ static rkl_status wait_host(rkl_plan_t p, hipStream_t st, HostWords* out) {
             __builtin_ia32_pause();
             continue;
         }
+        // a long wait: as the process has asked its waits to be
+        unsigned flags = 0;
+        (void)hipGetDeviceFlags(&flags);
+        flags &= hipDeviceScheduleMask;
+        if (flags == hipDeviceScheduleBlockingSync) HIPCHECK(hipStreamSynchronize(st), "read-back");
+        if (flags == hipDeviceScheduleYield) sched_yield();
         const hipError_t e = hipStreamQuery(st);
         if (e == hipErrorNotReady) continue;
         if (e != hipSuccess) return hipfail(e, "read-back");

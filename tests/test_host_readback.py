@@ -1,6 +1,6 @@
 """The calls that wait for a word from the GPU (rkl_superstep, rkl_dt_par,
 rkl_subcycle, rkl_aag), on the stand-in runtime of fake_hip.py: what they leave
-behind when they fail."""
+behind when they fail, and how they wait."""
 import fake_hip
 
 
@@ -52,5 +52,23 @@ for n, ndim in (((20, 20, 20), 3), ((200, 200, 200), 3), ((200, 200, 1), 2)):
     except rkl.RklError as e:
         assert e.status == rkl.RKL_ESTAGES
     assert get("unfinished") == 0, n
+    rkl.rkl_destroy(plan)
+''')
+
+
+def test_a_long_wait_sleeps_where_the_process_asked_for_it(tmp_path):
+    """hipDeviceScheduleBlockingSync (4): behind a stream that stays busy the
+    wait goes to hipStreamSynchronize instead of asking over and over"""
+    fake_hip.run(tmp_path, r'''
+put("flags", 4)
+put("pending", 1)
+put("queries", -1)
+put("query_limit", 50)
+for n, ndim in (((20, 20, 20), 3), ((200, 200, 1), 2)):
+    plan = rkl.rkl_plan([desc(n, ndim)])
+    before = get("syncs")
+    assert rkl.rkl_superstep(plan, 0, T, b, 1e-3, None) == 3
+    assert rkl.rkl_dt_par(plan, 0, T, None) == 1.0
+    assert get("syncs") == before + 2
     rkl.rkl_destroy(plan)
 ''')
