@@ -666,7 +666,7 @@ static rkl_status flat_start(rkl_plan_t p, int32_t g, const FlatTiling& t, const
 }
 
 // one group of a super-step; the pairs of stage buffers alternate
-static rkl_status flat_group(rkl_plan_t p, int32_t g, FlatLaunch& P, int group, hipStream_t st) {
+static rkl_status flat_group(rkl_plan_t p, int32_t g, FlatLaunch& P, int group, hipStream_t st, bool ask = false) {
     double *A = p->Ya + p->off[g], *B = p->Yb + p->off[g];
     P.kind = 1;
     P.group = group;
@@ -675,7 +675,7 @@ static rkl_status flat_group(rkl_plan_t p, int32_t g, FlatLaunch& P, int group, 
     P.out2 = group % 2 == 0 ? B : p->Fd;
     P.in1 = group % 2 == 0 ? p->Fc : A;
     P.in2 = group % 2 == 0 ? p->Fd : B;
-    HIPCHECK(launch_flat(p->precision, P, st), "stage group launch");
+    HIPCHECK(launch_flat(p->precision, P, st, ask), "stage group launch");
     return RKL_OK;
 }
 
@@ -686,9 +686,10 @@ static rkl_status flat_superstep_async(rkl_plan_t p, int32_t g, double* T, const
     if (rkl_status e = flat_start(p, g, p->flat[g], T, b, dt_hyp, 0, s_cap, &P, st)) return e;
     P.Tout = T;
     P.src.s_out = s_out;
-    P.groups = flat_groups(P.t, s_cap);
-    for (int k = 0; k < P.groups; ++k)
-        if (rkl_status e = flat_group(p, g, P, k, st)) return e;
+    P.launches = flat_groups(P.t, s_cap);
+    P.s_even = flat_even_from(P.t, P.launches);
+    for (int k = 0; k < P.launches; ++k)
+        if (rkl_status e = flat_group(p, g, P, k, st, flat_asks(P.t, k))) return e;
     return RKL_OK;
 }
 
@@ -764,6 +765,7 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
         // group 0 finds its share of the stages from s
         if ((st = flat_start(p, g, p->flat[g], T, b, dt_hyp, 0, p->smax, &P, s)) != RKL_OK) return st;
         P.Tout = T;
+        P.s_even = p->smax + 1;
         P.src.host = p->host;
         if ((st = flat_group(p, g, P, 0, s)) != RKL_OK) return st;
     } else {
@@ -786,8 +788,9 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
         return fail(RKL_ESTAGES, "stage count " + std::to_string(S) + " outside [" + std::to_string(smin) +
                                      ", smax=" + std::to_string(p->smax) + "]");
     if (use_flat(p, g)) {
-        P.groups = flat_groups(P.t, S);
-        for (int k = 1; k < P.groups; ++k)
+        P.launches = flat_groups(P.t, S);
+        P.s_even = 0;
+        for (int k = 1; k < P.launches; ++k)
             if ((st = flat_group(p, g, P, k, s)) != RKL_OK) return st;
         undo.on = false;
         return RKL_OK;

@@ -44,11 +44,26 @@ FlatTiling flat_tiling(int precision, const GridConst& gc);
 // the tiling of a single operator evaluation
 FlatTiling flat_tiling_once(int precision, const GridConst& gc);
 // groups of a super-step of s stages
-inline int flat_groups(const FlatTiling& t, int s) {
-    if (t.blocks() == 1) return 1;
+__host__ __device__ inline int flat_groups(const FlatTiling& t, int s) {
+    if (t.nt0 * t.nt1 == 1) return 1;
     const int g = (s + t.f - 1) / t.f;
     return g < 2 ? 2 : g;
 }
+
+// A super-step of s stages with `launches` enqueued before s is known spreads
+// its stages evenly over all of them while they are at most twice what it needs
+// (one without stages costs about as much as the set-up of one with few), that
+// is from this s on; below it is cut into the groups it needs.
+inline int flat_even_from(const FlatTiling& t, int launches) {
+    const int half = (launches + 1) / 2;
+    return half <= 2 ? 0 : t.f * (half - 1) + 1;
+}
+
+// Super-steps with s on the device: whether launch `group` asks for s before it
+// loads anything.  It then costs 2 to 4 us where s has no such group, against a
+// pass over the fields (1024 x 1024: 20 us), and 0.7 us (a small grid) to 17 us
+// (2048 x 2048) more where it has.  So only the groups past 64 stages do.
+inline bool flat_asks(const FlatTiling& t, int group) { return group > 1 && group >= flat_groups(t, 64); }
 
 struct FlatLaunch {
     int kind;            // 0 flux divergence, 1 super-step group, 2 Euler sub-steps
@@ -63,7 +78,9 @@ struct FlatLaunch {
     const void* b;
     GridState* state;
     const double* coef;  // RKL table, row (s, j) at 5 (s(s+1)/2 + j); NULL: RKL2 rows formed here
-    int group, groups;   // groups 0: as many as flat_groups gives for s
+    int group;
+    int launches;        // groups of a super-step of s >= s_even stages; of fewer: flat_groups(t, s),
+    int s_even;          // and later launches do nothing
     int smin, s_cap;     // s outside [smin, s_cap]: nothing is done
     FlatTiling t;
     GridConst gc;
@@ -74,10 +91,10 @@ struct FlatLaunch {
     double scale[kFlatEuler];   // kind 2: -tau_k (gamma-1)/rho
 };
 
-hipError_t launch_flat(int precision, const FlatLaunch& P, hipStream_t st);
+hipError_t launch_flat(int precision, const FlatLaunch& P, hipStream_t st, bool ask = false);   // ask: see flat_asks
 template <typename R>
-hipError_t launch_flat_r(const FlatLaunch& P, hipStream_t st);
-extern template hipError_t launch_flat_r<float>(const FlatLaunch&, hipStream_t);
-extern template hipError_t launch_flat_r<double>(const FlatLaunch&, hipStream_t);
+hipError_t launch_flat_r(const FlatLaunch& P, hipStream_t st, bool ask);
+extern template hipError_t launch_flat_r<float>(const FlatLaunch&, hipStream_t, bool);
+extern template hipError_t launch_flat_r<double>(const FlatLaunch&, hipStream_t, bool);
 
 }  // namespace rkl

@@ -91,8 +91,8 @@ FlatTiling flat_tiling_once(int precision, const GridConst& gc) {
     return t;
 }
 
-hipError_t launch_flat(int precision, const FlatLaunch& P, hipStream_t st) {
-    return precision == RKL_MIXED ? launch_flat_r<float>(P, st) : launch_flat_r<double>(P, st);
+hipError_t launch_flat(int precision, const FlatLaunch& P, hipStream_t st, bool ask) {
+    return precision == RKL_MIXED ? launch_flat_r<float>(P, st, ask) : launch_flat_r<double>(P, st, ask);
 }
 
 }  // namespace rkl

@@ -2,5 +2,5 @@
 #include "rkl_flat_kernel.h"
 
 namespace rkl {
-template hipError_t launch_flat_r<double>(const FlatLaunch&, hipStream_t);
+template hipError_t launch_flat_r<double>(const FlatLaunch&, hipStream_t, bool);
 }  // namespace rkl

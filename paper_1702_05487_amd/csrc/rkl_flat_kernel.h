@@ -35,19 +35,24 @@ __device__ __forceinline__ E ld(const E* base, unsigned i) {
 }
 
 // ND: dimensions (1 or 2).  One cell per thread, three barriers a stage (two
-// in 1-D).  The state and every input are asked for before anything waits.
-template <typename R, bool LIM, int SAT, int KM, int ND>
+// in 1-D).  The state and every input are asked for before anything waits;
+// ASK: s is asked for before everything else (flat_asks).
+template <typename R, bool LIM, int SAT, int KM, int ND, bool ASK>
 __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double rows[64 * 5];
     __shared__ double red[3][16];
     static_assert(kFlatThreads <= 16 * 64, "a slot of red per wave");
     __shared__ GridState sst;
+    const FlatTiling& t = P.t;
+    if (ASK) {
+        const int sa = P.state->s;
+        if (sa > P.s_cap || (sa < P.s_even && P.group >= flat_groups(t, sa))) return;
+    }
     const int tid = threadIdx.x, nt = blockDim.x;
     // the state as a former launch left it (the group that forms it does not use these)
     int s = P.state->s;
     double tref = P.state->tref, cdiv = P.state->cdiv;
-    const FlatTiling& t = P.t;
     const int n0 = P.gc.n0, n1 = P.gc.n1;
     const bool ox = P.gc.bc & 1, oy = P.gc.bc & 2, fx = P.gc.fixed & 1, fy = P.gc.fixed & 2;
 
@@ -158,7 +163,11 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     double scale = -P.gc.fac;
     if (P.kind == 1) {
         if (s < P.smin || s > P.s_cap) return;   // uniform over the launch
-        const int G = P.groups ? P.groups : (t.nt0 * t.nt1 == 1 ? 1 : max(2, (s + t.f - 1) / t.f));
+        int G = P.launches;
+        if (s < P.s_even) {
+            G = flat_groups(t, s);
+            if (P.group >= G) return;
+        }
         j0 = (int)(((unsigned)s * P.group + G - 1) / G) + 1;
         j1 = (int)(((unsigned)s * (P.group + 1) + G - 1) / G);
         last = P.group == G - 1;
@@ -292,34 +301,39 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     }
 }
 
+template <typename R, bool LIM, int SAT, int KM, int ND>
+static void flat_ask(const FlatLaunch& P, size_t lds, hipStream_t st, bool ask) {
+    if (ask) flat_kernel<R, LIM, SAT, KM, ND, true><<<P.t.blocks(), P.t.threads, lds, st>>>(P);
+    else flat_kernel<R, LIM, SAT, KM, ND, false><<<P.t.blocks(), P.t.threads, lds, st>>>(P);
+}
 template <typename R, bool LIM, int SAT, int KM>
-static void flat_nd(const FlatLaunch& P, size_t lds, hipStream_t st) {
-    if (P.gc.ndim == 2) flat_kernel<R, LIM, SAT, KM, 2><<<P.t.blocks(), P.t.threads, lds, st>>>(P);
-    else flat_kernel<R, LIM, SAT, KM, 1><<<P.t.blocks(), P.t.threads, lds, st>>>(P);
+static void flat_nd(const FlatLaunch& P, size_t lds, hipStream_t st, bool ask) {
+    if (P.gc.ndim == 2) flat_ask<R, LIM, SAT, KM, 2>(P, lds, st, ask);
+    else flat_ask<R, LIM, SAT, KM, 1>(P, lds, st, ask);
 }
 template <typename R, int SAT, int KM>
-static void flat_lim(const FlatLaunch& P, size_t lds, hipStream_t st) {
-    if (P.gc.limiter) flat_nd<R, true, SAT, KM>(P, lds, st);
-    else flat_nd<R, false, SAT, KM>(P, lds, st);
+static void flat_lim(const FlatLaunch& P, size_t lds, hipStream_t st, bool ask) {
+    if (P.gc.limiter) flat_nd<R, true, SAT, KM>(P, lds, st, ask);
+    else flat_nd<R, false, SAT, KM>(P, lds, st, ask);
 }
 template <typename R, int KM>
-static void flat_sat(const FlatLaunch& P, size_t lds, hipStream_t st) {
-    if (P.gc.saturation == 2) flat_lim<R, 2, KM>(P, lds, st);
-    else if (P.gc.saturation == 1) flat_lim<R, 1, KM>(P, lds, st);
-    else flat_lim<R, 0, KM>(P, lds, st);
+static void flat_sat(const FlatLaunch& P, size_t lds, hipStream_t st, bool ask) {
+    if (P.gc.saturation == 2) flat_lim<R, 2, KM>(P, lds, st, ask);
+    else if (P.gc.saturation == 1) flat_lim<R, 1, KM>(P, lds, st, ask);
+    else flat_lim<R, 0, KM>(P, lds, st, ask);
 }
 
 template <typename R>
-hipError_t launch_flat_r(const FlatLaunch& P, hipStream_t st) {
+hipError_t launch_flat_r(const FlatLaunch& P, hipStream_t st, bool ask) {
     const FlatTiling& t = P.t;
     // one cell, and one extra low face, per thread
     if (t.threads > kFlatThreads || t.w * t.h > t.threads || t.w + t.h > t.threads || t.f < 1 || P.gc.n2 != 1 ||
         P.gc.ndim > 2 || (P.kind == 2 && (P.count < 0 || P.count > kFlatEuler)))
         return hipErrorInvalidValue;
     const size_t lds = flat_lds<R>(t, P.gc.ndim, P.gc.fixed != 0);
-    if (P.gc.kmode == 0) flat_sat<R, 0>(P, lds, st);
-    else if (P.gc.kmode == 1) flat_sat<R, 1>(P, lds, st);
-    else flat_sat<R, 2>(P, lds, st);
+    if (P.gc.kmode == 0) flat_sat<R, 0>(P, lds, st, ask);
+    else if (P.gc.kmode == 1) flat_sat<R, 1>(P, lds, st, ask);
+    else flat_sat<R, 2>(P, lds, st, ask);
     return hipGetLastError();
 }
 

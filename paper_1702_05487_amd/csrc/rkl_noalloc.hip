@@ -111,7 +111,8 @@ extern "C" rkl_status rkl_superstep_noalloc(const rkl_grid_desc* grid, int32_t p
         P.M = f + 5 * N;
         P.b = b;
         P.state = state;
-        P.groups = flat_groups(ft, s_cap);
+        P.launches = flat_groups(ft, s_cap);
+        P.s_even = flat_even_from(ft, P.launches);
         P.smin = 2;
         P.s_cap = s_cap;
         P.t = ft;
@@ -127,7 +128,7 @@ extern "C" rkl_status rkl_superstep_noalloc(const rkl_grid_desc* grid, int32_t p
             if (re != hipSuccess) return hipfail(re, "reduce launch");
             P.src = partials_source(part, np, dt_hyp, 0, s_cap, s_out);
         }
-        for (int k = 0; k < P.groups; ++k) {
+        for (int k = 0; k < P.launches; ++k) {
             P.group = k;
             if (k > 0) P.derive = 0;
             const int o = k % 2 == 0 ? 0 : 2, i = 2 - o;
@@ -135,7 +136,7 @@ extern "C" rkl_status rkl_superstep_noalloc(const rkl_grid_desc* grid, int32_t p
             P.out2 = f + (o + 1) * N;
             P.in1 = f + i * N;
             P.in2 = f + (i + 1) * N;
-            const hipError_t le = launch_flat(precision, P, s);
+            const hipError_t le = launch_flat(precision, P, s, flat_asks(ft, k));
             if (le != hipSuccess) return hipfail(le, "stage group launch");
         }
         return RKL_OK;

@@ -1,0 +1,65 @@
+"""Super-steps with s on the device and an s_cap well above it: the same bits as
+with a close one (and as rkl_superstep), and each launch beyond s costs no more
+than an empty one.  An empty launch takes 2 to 4 us; 6 us each are allowed (a
+launch that loads the fields of the 2-D grid below takes 20 us and more)."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+from helpers import lib_desc, oracle_grid
+from paper_1702_05487_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+CASES = [((1000, 900, 1), 2, "fp64"), ((1000, 900, 1), 2, "mixed"), ((300000, 1, 1), 1, "fp64")]
+
+
+@pytest.mark.parametrize("k", range(len(CASES)), ids=["%dx%dx%d-%s" % (n + (p,)) for n, _, p in CASES])
+def test_loose_cap(k):
+    import torch
+    from paper_1702_05487_amd import rkl
+    n, ndim, precision = CASES[k]
+    print("loose cap", n, precision, flush=True)
+    h = (0.03, 0.04, 0.05)
+    rng = np.random.default_rng(k)
+    T = 1.0 + 0.001 * rng.random(n[::-1])
+    p = dict(inputs.SPITZER_MC_SAT, phi=0.05)
+    dt = inputs.midpoint_ratio(7) * oracle.dt_par(oracle_grid(n, h, ndim, p), T)
+    T = torch.from_numpy(T).to("cuda:0")
+    b = torch.from_numpy(inputs.unit_vectors(rng.standard_normal((3,) + n[::-1]))).to("cuda:0")
+    desc = lib_desc(n, h, ndim, p)
+    plan = rkl.Plan([desc], precision=precision)
+    b = b.to(plan.bdtype)
+    want = T.clone()
+    assert plan.superstep(want, b, dt) == 7
+    s_out = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+
+    def call(cap, W, alloc):
+        if alloc:
+            plan.superstep_async(W, b, dt, cap, s_out)
+        else:
+            rkl.superstep_noalloc(desc, W, b, dt, cap, s_out, precision=precision)
+
+    for alloc in (True, False):
+        if not alloc and n[0] * n[1] * n[2] > rkl.NOALLOC_MAX_CELLS:
+            continue
+        for cap in (7, 8, 23, 250):
+            W = T.clone()
+            call(cap, W, alloc)
+            assert s_out.item() == 7 and torch.equal(W, want), (alloc, cap)
+        took = {}
+        for cap in (8, 250):
+            best = 1e9
+            for _ in range(5):
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                for _ in range(5):
+                    call(cap, W, alloc)
+                torch.cuda.synchronize()
+                best = min(best, (time.perf_counter() - t) / 5)
+            took[cap] = best
+        print("  alloc %d: %.1f us, loose %.1f us" % (alloc, took[8] * 1e6, took[250] * 1e6), flush=True)
+        assert took[250] - took[8] <= 242 * 6e-6
+    plan.close()
