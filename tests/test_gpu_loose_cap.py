@@ -1,5 +1,5 @@
 """Super-steps with s on the device and an s_cap well above it: the same bits as
-with a close one (and as rkl_superstep), and each launch beyond s costs no more
+with a close one (and as rkl_superstep), and each launch beyond s costs little more
 than an empty one.  An empty launch takes 2 to 4 us; 6 us each are allowed (a
 launch that loads the fields of the 2-D grid below takes 20 us and more)."""
 import time
@@ -13,7 +13,8 @@ from paper_1702_05487_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
-CASES = [((1000, 900, 1), 2, "fp64"), ((1000, 900, 1), 2, "mixed"), ((300000, 1, 1), 1, "fp64")]
+CASES = [((1000, 900, 1), 2, "fp64"), ((1000, 900, 1), 2, "mixed"), ((300000, 1, 1), 1, "fp64"), ((64, 64, 64), 3, "mixed"),
+         ((140, 130, 120), 3, "fp64")]
 
 
 @pytest.mark.parametrize("k", range(len(CASES)), ids=["%dx%dx%d-%s" % (n + (p,)) for n, _, p in CASES])
