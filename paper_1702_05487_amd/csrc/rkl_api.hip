@@ -719,13 +719,14 @@ rkl_status rkl_flux_div(rkl_plan_t p, int32_t g, const double* T, const void* b,
     return RKL_OK;
 }
 
-// dt_par of grid g from T, read back
-static rkl_status read_dt_par(rkl_plan_t p, int32_t g, const double* T, double* dtp, hipStream_t s) {
+// dt_par of grid g from T, read back; mode 2 where the call ends with it, 1
+// where it goes on (or drains the stream)
+static rkl_status read_dt_par(rkl_plan_t p, int32_t g, const double* T, double* dtp, hipStream_t s, int mode) {
     rkl_status st = arm_host(p, s);
     if (st != RKL_OK) return st;
     Drain undo{s};
     StateSource q;
-    if ((st = extrema_source(p, g, T, 0.0, 1, p->smax, 1024, 1024, &q, s)) != RKL_OK) return st;
+    if ((st = extrema_source(p, g, T, 0.0, mode, p->smax, 1024, 1024, &q, s)) != RKL_OK) return st;
     q.host = p->host;
     HIPCHECK(launch_finalize(p->gc[g], q, p->state + g, nullptr, s), "finalize launch");
     HostWords w;
@@ -739,7 +740,7 @@ rkl_status rkl_dt_par(rkl_plan_t p, int32_t g, const double* T, double* dt_par_o
     rkl_status st = check_grid(p, g);
     if (st != RKL_OK) return st;
     if (!T || !dt_par_out) return fail(RKL_EINVAL, "NULL pointer");
-    return read_dt_par(p, g, T, dt_par_out, (hipStream_t)stream);
+    return read_dt_par(p, g, T, dt_par_out, (hipStream_t)stream, 2);
 }
 
 rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_hyp, int32_t* s_out,
@@ -1020,7 +1021,8 @@ rkl_status rkl_subcycle(rkl_plan_t p, int32_t g, double* T, const void* b, doubl
     if (max_sub < 1) return fail(RKL_EINVAL, "max_sub must be >= 1");
     hipStream_t s = (hipStream_t)stream;
     double dtp = 0.0;
-    if ((st = read_dt_par(p, g, T, &dtp, s)) != RKL_OK) return st;
+    if ((st = read_dt_par(p, g, T, &dtp, s, 1)) != RKL_OK) return st;
+    Drain undo{s};   // a call that enqueues no sub-step
     if (dt_hyp == 0.0 || std::isinf(dtp)) return RKL_OK;   // nothing to do
     // N_sub = ceil(dt_hyp / dt_par) forward-Euler sub-steps of dt_hyp / N_sub
     const double q = std::ceil(dt_hyp / dtp);
@@ -1030,6 +1032,7 @@ rkl_status rkl_subcycle(rkl_plan_t p, int32_t g, double* T, const void* b, doubl
     const double tau = dt_hyp / (double)nsub;
     st = euler_substeps(p, g, T, b, nsub, [tau](int64_t) { return tau; }, s);
     if (st != RKL_OK) return st;
+    undo.on = false;
     if (nsub_out) *nsub_out = nsub;
     return RKL_OK;
 }
@@ -1057,7 +1060,8 @@ rkl_status rkl_aag(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_
     if (max_s < 1) return fail(RKL_EINVAL, "max_s must be >= 1");
     hipStream_t s = (hipStream_t)stream;
     double dtp = 0.0;
-    if ((st = read_dt_par(p, g, T, &dtp, s)) != RKL_OK) return st;
+    if ((st = read_dt_par(p, g, T, &dtp, s, 1)) != RKL_OK) return st;
+    Drain undo{s};   // a call that enqueues no sub-step
     if (dt_hyp == 0.0 || std::isinf(dtp)) return RKL_OK;
     const double r = dt_hyp / dtp;
     int S = -1;
@@ -1074,6 +1078,7 @@ rkl_status rkl_aag(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_
     for (double& t : taus) t *= dt_hyp / sum;
     st = euler_substeps(p, g, T, b, S, [&taus](int64_t k) { return taus[k]; }, s);
     if (st != RKL_OK) return st;
+    undo.on = false;
     if (s_out) *s_out = S;
     return RKL_OK;
 }

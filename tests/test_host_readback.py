@@ -72,3 +72,19 @@ for n, ndim in (((20, 20, 20), 3), ((200, 200, 1), 2)):
     assert get("syncs") == before + 2
     rkl.rkl_destroy(plan)
 ''')
+
+
+def test_calls_with_nothing_to_do_leave_nothing_pending(tmp_path):
+    """rkl_subcycle and rkl_aag that enqueue no sub-step, and those refused"""
+    fake_hip.run(tmp_path, r'''
+plan = rkl.rkl_plan([desc((20, 20, 20))])
+put("pending", 1)
+for dtp, dt, status in ((1.0, 0.0, 0), (float("inf"), 1.0, 0), (1e-9, 1.0, rkl.RKL_ESTAGES)):
+    put("dt_par", dtp)
+    for call in (lambda: rkl.rkl_subcycle(plan, 0, T, b, dt, 10, None), lambda: rkl.rkl_aag(plan, 0, T, b, dt, 0.1, 10, None)):
+        try:
+            assert call() == 0 and status == 0
+        except rkl.RklError as e:
+            assert e.status == status
+        assert get("unfinished") == 0, (dtp, dt)
+''')
