@@ -25,8 +25,8 @@ struct StageLaunch {
 };
 
 // The buffers a routed stage reads, which follow from j alone, so that loads
-// need not wait for the state: Y_{j-1} and Y_{j-2} (a.Yout: the caller's T,
-// Y_0 and Y_s).
+// need not wait for the state (rkl_block.h): Y_{j-1} and Y_{j-2} (a.Yout: the
+// caller's T, Y_0 and Y_s).
 __device__ __forceinline__ void stage_inputs(const StageLaunch& P, TileArgs& a) {
     const int j = P.stage;
     if (!P.route.A || a.kind == 0 || a.kind == 3 || j == 1) return;   // stage 1 reads T
@@ -34,19 +34,24 @@ __device__ __forceinline__ void stage_inputs(const StageLaunch& P, TileArgs& a) 
     a.Ym2 = j == 2 ? a.Yout : (j & 1) ? P.route.A : P.route.B;   // Y_{j-2} sits where Y_j goes
 }
 
-// The output and the coefficients of this launch, with s and cdiv of the
-// grid's state; false where a routed stage does nothing, uniform over the
-// grid.  ext_able: the kernel can keep the extrema of the last stage.
-__device__ __forceinline__ bool stage_args(const StageLaunch& P, bool ext_able, int s, double cdiv, TileArgs& a) {
+// The buffers and the coefficients of this launch, with s and cdiv of the
+// grid's state (get_s, get_cdiv: asked for where they are needed, since each wait
+// for a scalar at the start of a kernel costs 0.3 to 0.5 us); false where a
+// routed stage does nothing, uniform over the grid.  ext_able: the kernel can
+// keep the extrema of the last stage.
+template <typename S, typename C>
+__device__ __forceinline__ bool stage_args(const StageLaunch& P, bool ext_able, S get_s, C get_cdiv, TileArgs& a) {
     if (a.kind == 0) {
         a.scale = -P.fac;
     } else if (a.kind == 3) {
         a.scale = P.sub_scale;
     } else {
+        const int s = get_s();
         if (P.route.A) {
             // the stage sequence was launched up to s_cap without knowing s
             const int j = P.stage;
             if (j > s || s < P.route.s_min || s > P.route.s_cap) return false;
+            stage_inputs(P, a);
             // Y_s goes to T, but not from stage 1, which reads T around each cell
             if (j < s || j == 1) a.Yout = (j & 1) ? P.route.A : P.route.B;
             a.ext = ext_able && P.ext.part && j == s;
@@ -57,7 +62,7 @@ __device__ __forceinline__ bool stage_args(const StageLaunch& P, bool ext_able, 
         a.omn = cf[2];
         a.mut = cf[3];
         a.gt = cf[4];
-        a.scale = -cdiv;
+        a.scale = -get_cdiv();
     }
     return true;
 }
@@ -124,10 +129,9 @@ __global__ __launch_bounds__(BX* BY) void stage_kernel(StageLaunch P) {
     a.y0 = tile_y * BY;
     a.z0 = zc * P.bz;
     a.z1 = min(a.z0 + P.bz, a.n2);
-    stage_inputs(P, a);
     const double tref = sizeof(R) == 4 ? P.state->tref : 0.0;
     constexpr bool FIX = MODE == 1 || MODE == 3;
-    if (!stage_args(P, FIX, P.state->s, P.state->cdiv, a)) return;
+    if (!stage_args(P, FIX, [&] { return P.state->s; }, [&] { return P.state->cdiv; }, a)) return;
     const FaceK<R> fk = make_facek<R>(P.kappa0, P.kexp, P.kperp, P.satq, tref);
     if constexpr (FIX) {
         using PF = typename std::conditional<three_waves<R, BX, BY>(SAT, KM), Prefetch<1, 1, 0, true>,
