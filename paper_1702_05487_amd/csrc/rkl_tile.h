@@ -486,26 +486,36 @@ __device__ __forceinline__ TileExt run_tile(const TileArgs& a, const FaceK<R>& f
         int pzt = bidx(z0 + TD, n2, oz), pzb = bidx(z0 - 1 + BD, n2, oz);   // planes k+2+TD and k+1+BD
         const auto next = [&](int p, int m) { return oz ? min(max(m, 0), n2 - 1) : (p + 1 == n2 ? 0 : p + 1); };
 
-        // prologue (P = 0 at k = z0 - 2): T(k .. k+1+TD), b(k+1 .. k+BD)
+        // prologue (P = 0 at k = z0 - 2): T(k .. k+1+TD), b(k+1 .. k+BD), the loads of
+        // a column together, so that none waits for the one before it
+        size_t pp[2 + TD];
 #pragma unroll
-        for (int m = 0; m < 2 + TD; ++m) {
-            const double* p = a.Yin + (size_t)bidx(z0 - 2 + m, n2, oz) * plane;
-            if (own) tq[m] = tld(p, z0 - 2 + m, oxy, gco);
-            if (hjob) {
-                const double v = tld(p, z0 - 2 + m, hxy, gch);
-                if (m < 2) {
-                    hq[m] = to_r<R>(v, tref);
-                    L.T[m][hslot] = hq[m];
-                } else {
-                    th[(m - 2) % LH] = v;
-                }
+        for (int m = 0; m < 2 + TD; ++m) pp[m] = (size_t)bidx(z0 - 2 + m, n2, oz) * plane;
+        if (own) {
+#pragma unroll
+            for (int m = 0; m < 2 + TD; ++m) tq[m] = tld(a.Yin + pp[m], z0 - 2 + m, oxy, gco);
+#pragma unroll
+            for (int m = 1; m <= BD; ++m) {
+                R* bl = ob[m % LB];
+                bl[0] = b0[pp[m] + oxy]; bl[1] = b1[pp[m] + oxy]; bl[2] = b2[pp[m] + oxy];
             }
         }
+        if (hjob) {
+            double h0[2];              // planes k, k+1
 #pragma unroll
-        for (int m = 1; m <= BD; ++m) {
-            const size_t pb = (size_t)bidx(z0 - 2 + m, n2, oz) * plane;
-            if (own) { ob[m % LB][0] = b0[pb + oxy]; ob[m % LB][1] = b1[pb + oxy]; ob[m % LB][2] = b2[pb + oxy]; }
-            if (djob) { pbd[m % LD][0] = b0[pb + hxy]; pbd[m % LD][1] = b1[pb + hxy]; pbd[m % LD][2] = b2[pb + hxy]; }
+            for (int m = 0; m < 2 + TD; ++m) (m < 2 ? h0[m] : th[(m - 2) % LH]) = tld(a.Yin + pp[m], z0 - 2 + m, hxy, gch);
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                hq[m] = to_r<R>(h0[m], tref);
+                L.T[m][hslot] = hq[m];
+            }
+        }
+        if (djob) {
+#pragma unroll
+            for (int m = 1; m <= BD; ++m) {
+                R* bl = pbd[m % LD];
+                bl[0] = b0[pp[m] + hxy]; bl[1] = b1[pp[m] + hxy]; bl[2] = b2[pp[m] + hxy];
+            }
         }
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
