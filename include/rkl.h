@@ -110,7 +110,7 @@ typedef struct {
 
 typedef struct {
     int32_t precision;    /* RKL_FP64 or RKL_MIXED */
-    int32_t variant;      /* stencil kernel variant (see rkl_variant_info); -1 = library default */
+    int32_t variant;      /* stencil kernel variant (see rkl_variant_info); -1 = library default, which is 0 */
     int32_t smax;         /* largest stage count accepted (coefficient table size); 0 = 1024
                              for one grid, 64 for several (a batched super-step issues
                              one stage launch per stage up to smax) */
@@ -336,16 +336,23 @@ rkl_status rkl_query(rkl_plan_t plan, int32_t grid, int32_t *last_s, double *las
 
 /*
  * Stencil kernel variants: rkl_variant_count() of them.  rkl_variant_info
- * fills the workgroup tile (tile_x x tile_y cells, z-chunks of at most tile_z
- * planes; a grid too small to fill the GPU with them takes shorter ones) and the stages per launch `fuse` (any pointer may be NULL):
- *   fuse 1: one RKL2 stage per launch, output tile = tile_x x tile_y;
+ * fills the workgroup tile (tile_x x tile_y cells, z-chunks of tile_z planes)
+ * and the stages per launch `fuse` (any pointer may be NULL):
+ *   variant 0 (the default, also of a zeroed rkl_options): one RKL2 stage per
+ *           launch, the kernel chosen for the grid: the tile given with
+ *           z-chunks of at most tile_z planes, shorter ones where they would
+ *           leave the GPU idle, or blocks of 16 x 4 x 4 cells;
+ *   fuse 1, any other: one RKL2 stage per launch, output tile = tile_x x
+ *           tile_y, z-chunks of tile_z planes whatever the grid (grids with
+ *           fixed axes: tiles of 16 x 16 with those chunks);
  *   fuse F = 2, 3, 4: stages j..j+F-1 in one launch (temporal fusion of
  *           Appendix A's recurrence; 2 <= j, j+F-1 < s; the last stage, and a
  *           remainder shorter than F, run one stage per launch), output tile
  *           (tile_x-2(F-1)) x (tile_y-2(F-1)): the tile's border rings are
  *           recomputed by the neighbouring tiles.  RKL_MIXED plans of periodic
  *           3-D grids only; selecting one allocates two more FP64 stage
- *           buffers.
+ *           buffers.  Their one-stage launches are chosen as in variant 0.
+ * 1-D and 2-D grids run several stages per launch whatever the variant.
  * rkl_set_variant selects a variant for a plan (RKL_EINVAL if the plan
  * cannot use it, RKL_ENOMEM); the autotuner calls it.
  */
@@ -374,7 +381,8 @@ rkl_status rkl_profile_read(rkl_plan_t plan, int32_t fuse, double *ms, int64_t *
 
 /*
  * rkl_autotune: time every stencil variant the plan can use (tile shape,
- * z-chunk, stages per launch) on `grid`
+ * z-chunk, stages per launch; those that launch the same kernels on this grid
+ * once, under the lowest index) on `grid`
  * with the caller's fields -- `reps` super-steps of dt_hyp each, on a
  * plan-owned scratch copy of T (T itself is not modified) -- select the
  * fastest for the plan and return its index and average super-step time.

@@ -1,6 +1,7 @@
 // rkl_api.hip -- host side of librkl's C ABI (include/rkl.h): descriptor
 // validation, plan scratch, the RKL2 coefficient table, and the launch
 // sequences of the single-grid entry points.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <sched.h>
@@ -1105,8 +1106,20 @@ rkl_status rkl_autotune(rkl_plan_t p, int32_t g, const double* T, const void* b,
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
         res = fail(RKL_EDEVICE, "autotune events");
     }
+    std::vector<Variant> timed;
     for (int v = 0; res == RKL_OK && v < variant_count(); ++v) {
-        if (!variant_ok(p, variant_get(v))) continue;
+        const Variant x = variant_get(v);
+        if (!variant_ok(p, x)) continue;
+        // variants that run the same launches here are timed once (1-D and 2-D
+        // grids: any; else those of equal tiles and chunks)
+        Variant w = x.fuse == 1 ? fit_variant(p->precision, x, p->gc[g]) : x;
+        w.bz = std::min(w.bz, p->gc[g].n2);
+        const auto same = [&](const Variant& o) {
+            return use_flat(p, g) ||
+                   (o.bx == w.bx && o.by == w.by && o.bz == w.bz && o.fuse == w.fuse && o.block == w.block);
+        };
+        if (std::any_of(timed.begin(), timed.end(), same)) continue;
+        timed.push_back(w);
         res = select_variant(p, v);
         if (res != RKL_OK) break;
         // one untimed super-step from the caller's T, then reps timed ones

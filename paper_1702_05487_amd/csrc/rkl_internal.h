@@ -219,17 +219,19 @@ __device__ __forceinline__ void block_state(const GridConst& g, const StateSourc
 }
 
 // Kernel variants of the single-grid stencil: tile shape, z-chunk length and
-// stages per launch (1, or 2 for the fused kernel).
+// stages per launch (1, or 2 to 4 for the fused kernel).
 struct Variant {
     int bx, by, bz, fuse;
+    bool exact = false;   // z-chunks of bz planes whatever the grid
     bool block = false;   // fitted: blocks of bx x by x bz cells (rkl_block.h) instead of z-marched tiles
 };
 constexpr int kBlockX = 16, kBlockY = 4, kBlockZ = 4;
 int variant_count();
 Variant variant_get(int v);
-constexpr int kDefaultVariant = 1;   // 32 x 8 tile, z-chunks of at most 64 planes
-// the variant as a one-stage launch on grid gc runs it: its z-chunk shortened
-// where the grid would leave CUs idle, the 16 x 16 tile for fixed axes
+constexpr int kDefaultVariant = 0;   // the kernel by the grid (fit_variant)
+// The variant as a one-stage launch on grid gc runs it: fixed axes take the 16 x
+// 16 tile; a variant that is not exact takes the z-chunk, and if that is faster
+// the blocks, that suit the grid.
 Variant fit_variant(int precision, Variant v, const GridConst& gc);
 
 // Launchers (enqueue only; return the HIP error of the launch).

@@ -14,12 +14,14 @@ namespace rkl {
 // (bx, by) are compile-time tile shapes; bz is the z-chunk length per block;
 // fuse is the number of stages per launch (F = 2..4: rkl_fused.hip, where
 // (bx, by) is the region of a workgroup and (bx-2(F-1), by-2(F-1)) its
-// output tile).
+// output tile).  Variant 0 is the library's choice by the grid, with chunks of
+// at most 64 planes; so are the one-stage launches of the fused variants.
 static const Variant kVariants[] = {
-    {32, 8, 32, 1}, {32, 8, 64, 1}, {64, 4, 32, 1}, {64, 4, 64, 1}, {16, 16, 32, 1}, {16, 16, 64, 1},
-    {32, 8, 16, 1}, {64, 4, 16, 1},
-    {16, 16, 32, 2}, {16, 16, 64, 2}, {32, 8, 32, 2}, {32, 8, 64, 2},
-    {16, 16, 32, 3}, {16, 16, 64, 3}, {16, 16, 32, 4}, {16, 16, 64, 4},
+    {32, 8, 64, 1},        {32, 8, 64, 1, true},  {64, 4, 32, 1, true}, {64, 4, 64, 1, true}, {16, 16, 32, 1, true},
+    {16, 16, 64, 1, true}, {32, 8, 16, 1, true},  {64, 4, 16, 1, true},
+    {16, 16, 32, 2},       {16, 16, 64, 2},       {32, 8, 32, 2},       {32, 8, 64, 2},
+    {16, 16, 32, 3},       {16, 16, 64, 3},       {16, 16, 32, 4},      {16, 16, 64, 4},
+    {32, 8, 32, 1, true},
 };
 int variant_count() { return (int)(sizeof(kVariants) / sizeof(kVariants[0])); }
 Variant variant_get(int v) { return kVariants[v]; }
@@ -133,7 +135,11 @@ static hipError_t launch_prec(const StageLaunch& P, int nblocks, const Variant& 
 // FP64 49.3 / 12.5 / 9.8 us, 96^3 FP64 49.9 / 23.5 / 24.1 us, 128^3 FP64 50.7 /
 // 42.4 / 50.1 us, 150 x 127 x 101 mixed 45.2 / 30.3 / 33.4 us.
 Variant fit_variant(int precision, Variant v, const GridConst& gc) {
-    if (gc.fixed) v = Variant{16, 16, v.bz, 1};   // the tile shape of the ghost-loading kernel
+    if (gc.fixed) {
+        v.bx = v.by = 16;   // the tile shape of the ghost-loading kernel
+        v.fuse = 1;
+    }
+    if (v.exact) return v;
     const bool f32 = precision == RKL_MIXED;
     const bool three = !f32 && gc.saturation && gc.kmode != 2 && !gc.fixed && v.bx != 64;   // as three_waves
     const int per_cu = f32 || three ? 3 : 2;
@@ -162,7 +168,8 @@ Variant fit_variant(int precision, Variant v, const GridConst& gc) {
     }
     v.bz = best;
     if (gc.ndim == 3 && !gc.fixed && (int64_t)gc.n0 * gc.n1 * gc.n2 < (int64_t)1 << 29) {   // 32-bit byte offsets
-        Variant w{kBlockX, kBlockY, kBlockZ, 1, true};
+        Variant w{kBlockX, kBlockY, kBlockZ, 1};
+        w.block = true;
         const double nb = (double)stage_blocks(w, gc);
         const double block = f32 ? std::max(5.0, 4.0 + 0.0035 * nb) : std::max(5.4, 4.1 + 0.0056 * nb);
         if (block < 4.0 + c[per_cu] * best_cost) return w;

@@ -1,0 +1,77 @@
+"""Which kernel a call launches, with how many workgroups, on the stand-in
+runtime of fake_hip.py: the variants launch the tiles and chunks that
+rkl_variant_info names."""
+import fake_hip
+
+SIZES = "((37, 11, 70), (48, 40, 36), (20, 20, 20), (5, 3, 1), (500, 251, 13), (100, 90, 200))"
+
+
+def test_a_variant_runs_its_own_tile_and_chunk(tmp_path):
+    """every variant but 0, whatever the grid; a small 3-D grid must not end up in
+    the block kernel unless the variant is left to the library"""
+    fake_hip.run(tmp_path, r'''
+up = lambda a, b: -(-a // b)
+seen = set()
+for n in %s:
+    for prec in (0, 1):
+        for v in range(1, rkl.rkl_variant_count()):
+            x, y, z, fuse = rkl.rkl_variant_info(v)
+            if fuse != 1:
+                continue
+            plan = rkl.rkl_plan([desc(n)], precision=prec, variant=v)
+            for call in (lambda: rkl.rkl_superstep(plan, 0, T, b, 1e-3, None), lambda: rkl.rkl_flux_div(plan, 0, T, b, out, None),
+                         lambda: rkl.rkl_subcycle(plan, 0, T, b, 2.5, 9, None),
+                         lambda: rkl.rkl_supersteps_async(plan, 0, T, b, 1e-3, 2, 4, None, None)):
+                hip.fake_reset()
+                call()
+                got = {l[:2] for l in launches() if "finalize" not in l[0] and "reduce" not in l[0]}
+                want = up(n[0], x) * up(n[1], y) * up(n[2], z)
+                assert got and all("stage_kernel" in k and (", %%d, %%d, " %% (x, y)) in k and g == want for k, g in got), (n, v, got, want)
+            seen.add((x, y, z))
+            rkl.rkl_destroy(plan)
+assert len(seen) == 8, seen
+''' % SIZES)
+
+
+def test_zeroed_options_give_the_default(tmp_path):
+    fake_hip.run(tmp_path, r'''
+for n, ndim in [(m, 3) for m in %s] + [((64, 64, 1), 2), ((400, 1, 1), 1)]:
+    got = []
+    for v in (-1, 0):
+        plan = rkl.rkl_plan([desc(n, ndim)], variant=v)
+        hip.fake_reset()
+        rkl.rkl_superstep(plan, 0, T, b, 1e-3, None)
+        got.append(launches())
+        rkl.rkl_destroy(plan)
+    assert got[0] == got[1], n
+''' % SIZES)
+
+
+def test_autotune_times_each_form_once(tmp_path):
+    """variants that launch the same kernels on a grid are one candidate"""
+    fake_hip.run(tmp_path, r'''
+for n, ndim, edges, prec in (((20, 20, 1), 2, (0, 0, 0), 0), ((20, 20, 20), 3, (0, 0, 0), 0), ((37, 11, 40), 3, (0, 1, 0), 0),
+                             ((20, 20, 20), 3, (0, 0, 0), 1), ((24, 24, 24), 3, (2, 0, 0), 0)):
+    plan = rkl.rkl_plan([desc(n, ndim, edges=edges)], precision=prec)
+    for ax in range(3):
+        if edges[ax] == 2:
+            rkl.rkl_set_ghosts(plan, 0, ax, T, T)
+    forms = set()
+    for v in range(rkl.rkl_variant_count()):
+        try:
+            rkl.rkl_set_variant(plan, v)
+        except rkl.RklError:
+            continue                       # fused variants: mixed, periodic 3-D grids
+        put("s", 9)
+        hip.fake_reset()
+        rkl.rkl_superstep(plan, 0, T, b, 1e-3, None)
+        forms.add(tuple(launches()))
+    starts = sum("finalize" in l[0] or ndim == 2 for l in min(forms, key=len))   # of one super-step
+    assert starts == 1
+    hip.fake_reset()
+    best, ms = rkl.rkl_autotune(plan, 0, T, b, 1e-3, 2, None)
+    got = sum("finalize" in l[0] or ndim == 2 for l in launches())
+    assert got == 3 * len(forms), (n, got, len(forms))     # one untimed and two timed each
+    assert best == 0 or ndim == 3
+    rkl.rkl_destroy(plan)
+''')
