@@ -117,62 +117,93 @@ static hipError_t launch_prec(const StageLaunch& P, int nblocks, const Variant& 
 // each plane a chain of one barrier, LDS exchanges and three face evaluations,
 // so a launch takes as long as its longest march times the rounds of resident
 // workgroups.  A chunk of bz planes costs bz + 2 plane iterations (the two
-// before z0 fill the rings); an iteration takes c[k] microseconds with k
-// workgroups on a CU (MC, T^2.5 and saturated flux; measured with 64^3 to
-// 192^3 grids, k = 1, 2, 3; three mixed, two FP64 or three saturated FP64
-// workgroups fit a CU's registers), and a launch 4 us besides.  Short chunks
-// give a small grid enough workgroups for the 256 CUs, long ones keep the two
-// extra iterations and the halo planes cheap.  The last, partly filled round is priced half by its share
-// of the slots and half as a round of its own: workgroups of different rounds
-// overlap, but not fully.
+// before z0 fill the rings); an iteration takes chunk[k] microseconds with k
+// workgroups on a CU.  Short chunks give a small grid enough workgroups for the
+// 256 CUs, long ones keep the two extra iterations and the halo planes cheap.
+// The last, partly filled round is priced half by its share of the slots and half
+// as a round of its own: workgroups of different rounds overlap, but not fully.
 //
-// Blocks of 16 x 4 x 4 cells (rkl_block.h): no march, so the least a launch
-// takes is 5.4 us (FP64; mixed 5.0), but 0.0056 us (0.0035) more per block
-// against 0.0025 (0.0016) for 256 marched cells of a large grid.
+// Blocks of 16 x 4 x 4 cells (rkl_block.h) have no march; n of them take
+// max(least, b0 + b1 n) microseconds.  The march's own time for the comparison is
+// start + (bz + lead) x rounds with it[k] an iteration and `mix` of the last
+// round as its own.  start to b1 are fits to 27 sizes from 8 x 8 x 512 to 384^3,
+// every chunk, with the kernels as they are now (rms 2 to 5 %; FP64 without
+// saturation 9 %).  Beyond 2^22 cells the memory sets the time of both, and the
+// march reads less of it.  FP64 with pow() marches at one wave per SIMD (its
+// kernel takes 264 registers, the block kernel 127), so blocks stay faster there
+// up to the largest grid measured (384^3).
 //
-// Measured per stage, 32-plane chunks / the chunk taken here / blocks:
-// 45 x 33 x 29 FP64 37.8 / 9.0 / 5.5 us, 64^3 mixed 38.0 / 9.4 / 7.4 us, 64^3
-// FP64 49.3 / 12.5 / 9.8 us, 96^3 FP64 49.9 / 23.5 / 24.1 us, 128^3 FP64 50.7 /
-// 42.4 / 50.1 us, 150 x 127 x 101 mixed 45.2 / 30.3 / 33.4 us.
+// Measured, us a stage, best march (its chunk) / blocks; x: not taken:
+//                     FP64, T^2.5, saturated  mixed, the same     FP64, T^1.7, upwind
+//   24^3              x 7.5 (1)    5.8        x 6.6 (1)    5.4    x 11.1 (1)     7.8
+//   64^3              x 11.2 (2)   9.4        x 9.2 (2)    7.6    x 22.5 (4)    14.9
+//   88^3              19.2 (4)  x 19.1        13.5 (4)  x 13.7    x 56.3 (6)    34.7
+//   112^3             x 36.0 (10) 32.6        x 23.0 (10) 21.9    x 107 (28)    60.5
+//   128^3             42.5 (12) x 46.0        26.7 (12) x 29.9    x 124 (32)    90.2
+//   150 x 127 x 101   43.2 (12) x 46.2        26.8 (12) x 30.6    x 128 (34)    90.3
+//   65 x 65 x 300     x 50.7 (16) 34.4        x 30.0 (16) 24.0    x 154 (20)    68.9
+//   512 x 512 x 1     13.7 (1)  x 22.8        11.2 (1)  x 15.8    35.7 (1)    x 43.7
+//   512 x 512 x 4     x 26.0 (4)  24.2        x 19.5 (4)  17.0    x 80.7 (4)    44.6
+//   192^3             126 (16)  x 159         75.1 (39) x 101     x 437 (39)     285
 Variant fit_variant(int precision, Variant v, const GridConst& gc) {
     if (gc.fixed) {
         v.bx = v.by = 16;   // the tile shape of the ghost-loading kernel
         v.fuse = 1;
     }
     if (v.exact) return v;
+    if (gc.fixed) v.bz = std::min(v.bz, 32);   // 256^3 mixed: 32 planes 222, 64 planes 254 us
     const bool f32 = precision == RKL_MIXED;
-    const bool three = !f32 && gc.saturation && gc.kmode != 2 && !gc.fixed && v.bx != 64;   // as three_waves
-    const int per_cu = f32 || three ? 3 : 2;
-    static const double c32[] = {0.0, 1.03, 1.3, 1.6}, c64[] = {0.0, 1.3, 1.95},
-                        c64s[] = {0.0, 1.5, 2.35, 3.15};
-    const double* c = f32 ? c32 : three ? c64s : c64;
+    const bool pow_law = gc.kmode == 2, sat = gc.saturation != 0;
+    struct Price {
+        int per_cu;   // workgroups on a CU, by registers and LDS
+        double chunk[5];
+        double start, lead, mix, it[4], least, b0, b1;
+    };
+    static const Price prices[] = {
+        // FP64: classical, saturated (three_waves), pow()
+        {2, {0, 1.3, 1.95}, 2.9, 2.4, 0.81, {0, 1.16, 1.57}, 5.25, 4.4, 0.0038},
+        {3, {0, 1.5, 2.35, 3.15}, 3.9, 1.3, 0.68, {0, 1.63, 2.20, 2.87}, 5.75, 4.7, 0.0048},
+        {1, {0, 3.6}, 2.8, 1.3, 1.0, {0, 3.6}, 5.75, 5.7, 0.0099},
+        // mixed
+        {3, {0, 1.03, 1.3, 1.6}, 3.0, 2.6, 0.81, {0, 0.98, 1.13, 1.36}, 5.1, 4.2, 0.0027},
+        {3, {0, 1.03, 1.3, 1.6}, 3.1, 2.2, 0.75, {0, 1.13, 1.34, 1.62}, 5.4, 4.4, 0.0031},
+        {3, {0, 1.03, 1.3, 1.6}, 3.7, 1.1, 0.67, {0, 2.28, 2.82, 3.48}, 5.4, 5.3, 0.0057},
+        // fixed axes (the runtime-shaped kernel; no blocks): FP64, mixed
+        {3, {0, 1.98, 2.48, 3.83}},
+        {4, {0, 1.66, 1.92, 2.21, 2.9}},
+    };
+    const Price& p = prices[gc.fixed ? 6 + f32 : 3 * f32 + (pow_law ? 2 : sat)];
     const int64_t tiles = (int64_t)((gc.n0 + v.bx - 1) / v.bx) * ((gc.n1 + v.by - 1) / v.by);
-    const int64_t slots = 256 * per_cu;
+    const int64_t slots = 256 * p.per_cu;
+    // rounds of nb workgroups, the last one mixed of itself and its share
+    const auto rounds = [&](int64_t nb, const double* c, double mix) {
+        const int64_t full = nb / slots, rem = nb % slots;
+        if (!rem) return (double)full;
+        const double share = (double)rem / slots, own = c[(rem + 255) / 256] / c[p.per_cu];
+        return full ? full + mix * own + (1.0 - mix) * share : own;
+    };
     int best = v.bz;
     double best_cost = INFINITY;
     for (int z = std::min(v.bz, gc.n2); z >= 1; --z) {
         const int nzc = (gc.n2 + z - 1) / z;
         const int bz = (gc.n2 + nzc - 1) / nzc;   // chunks of equal length
         if (bz != z) continue;
-        const int64_t nb = tiles * nzc, full = nb / slots, rem = nb % slots;
-        double rounds = (double)full;
-        if (rem) {
-            const double share = (double)rem / slots, own = c[(rem + 255) / 256] / c[per_cu];
-            rounds += full ? 0.5 * (share + own) : own;
-        }
-        const double cost = (bz + 2) * rounds;
+        const double cost = (bz + 2) * rounds(tiles * nzc, p.chunk, 0.5);
         if (cost < best_cost) {
             best_cost = cost;
             best = bz;
         }
     }
     v.bz = best;
-    if (gc.ndim == 3 && !gc.fixed && (int64_t)gc.n0 * gc.n1 * gc.n2 < (int64_t)1 << 29) {   // 32-bit byte offsets
+    const int64_t N = (int64_t)gc.n0 * gc.n1 * gc.n2;
+    if (gc.ndim == 3 && !gc.fixed && N < (int64_t)1 << 29 &&   // 32-bit byte offsets
+        (N <= (int64_t)1 << 22 || (pow_law && !f32))) {
         Variant w{kBlockX, kBlockY, kBlockZ, 1};
         w.block = true;
-        const double nb = (double)stage_blocks(w, gc);
-        const double block = f32 ? std::max(5.0, 4.0 + 0.0035 * nb) : std::max(5.4, 4.1 + 0.0056 * nb);
-        if (block < 4.0 + c[per_cu] * best_cost) return w;
+        const double march = p.start + (best + p.lead) * p.it[p.per_cu] *
+                                           rounds(tiles * ((gc.n2 + best - 1) / best), p.it, p.mix);
+        // near a tie blocks were the faster ones (112^3, 65 x 65 x 300, 256 x 256 x 3 mixed)
+        if (std::max(p.least, p.b0 + p.b1 * stage_blocks(w, gc)) < 1.03 * march) return w;
     }
     return v;
 }

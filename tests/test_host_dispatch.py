@@ -1,6 +1,6 @@
 """Which kernel a call launches, with how many workgroups, on the stand-in
 runtime of fake_hip.py: the variants launch the tiles and chunks that
-rkl_variant_info names."""
+rkl_variant_info names, the default the form that measured fastest."""
 import fake_hip
 
 SIZES = "((37, 11, 70), (48, 40, 36), (20, 20, 20), (5, 3, 1), (500, 251, 13), (100, 90, 200))"
@@ -73,5 +73,34 @@ for n, ndim, edges, prec in (((20, 20, 1), 2, (0, 0, 0), 0), ((20, 20, 20), 3, (
     got = sum("finalize" in l[0] or ndim == 2 for l in launches())
     assert got == 3 * len(forms), (n, got, len(forms))     # one untimed and two timed each
     assert best == 0 or ndim == 3
+    rkl.rkl_destroy(plan)
+''')
+
+
+def test_default_form(tmp_path):
+    """sizes at which one form measured at least 10 % faster than the other
+    (us a stage, march / blocks)"""
+    fake_hip.run(tmp_path, r'''
+FP64, MIXED = 0, 1
+MC, SAT, POW = dict(sat=0), dict(sat=1), dict(sat=2, law=1.7)
+CASES = [  # size, precision, physics, blocks
+    ((24, 24, 24), FP64, MC, True), ((24, 24, 24), MIXED, POW, True),          # 7.2 / 5.4, 8.2 / 6.6
+    ((64, 64, 64), FP64, SAT, True), ((64, 64, 64), MIXED, MC, True),          # 11.2 / 9.4, 8.7 / 7.2
+    ((104, 104, 104), FP64, MC, True), ((112, 112, 112), FP64, MC, True),      # 28.7 / 24.9, 35.0 / 28.8
+    ((128, 128, 128), FP64, MC, False), ((144, 144, 144), MIXED, SAT, False),  # 35.7 / 41.9, 35.7 / 43.0
+    ((160, 160, 160), FP64, SAT, False), ((192, 192, 192), MIXED, MC, False),  # 76.4 / 85.2, 68.1 / 95.4
+    ((128, 128, 128), FP64, POW, True), ((256, 256, 256), FP64, POW, True),    # 124 / 90, 915 / 654
+    ((256, 256, 256), MIXED, POW, False), ((384, 384, 384), FP64, POW, True),  # 307 / 386, 3181 / 2190
+    ((512, 512, 1), FP64, MC, False), ((512, 512, 1), FP64, POW, False),       # 14.1 / 21.2, 35.7 / 43.7
+    ((512, 512, 4), FP64, MC, True), ((512, 512, 4), FP64, POW, True),         # 25.6 / 22.2, 80.7 / 44.6
+    ((512, 512, 6), MIXED, SAT, False), ((65, 65, 300), FP64, SAT, True),      # 24.7 / 29.6, 50.7 / 34.4
+    ((1000, 1000, 5), FP64, SAT, False), ((8, 8, 512), MIXED, SAT, True),      # 102 / 162, 7.0 / 5.2
+]
+for n, prec, phys, blocks in CASES:
+    plan = rkl.rkl_plan([desc(n, **phys)], precision=prec)
+    hip.fake_reset()
+    rkl.rkl_superstep(plan, 0, T, b, 1e-3, None)
+    got = any("block_kernel" in l[0] for l in launches())
+    assert got == blocks, (n, prec, phys)
     rkl.rkl_destroy(plan)
 ''')
