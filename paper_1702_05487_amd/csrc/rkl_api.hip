@@ -202,7 +202,8 @@ static rkl_status ensure_batch(rkl_plan_s* p) {
         // the batched stage routing writes stage j = s into T, which needs s >= 2
         if (p->scheme != RKL_RKL2) return fail(RKL_EINVAL, "the batched super-step implements RKL2 only");
         std::string why;
-        rkl_status st = batch_create(p->desc, p->gc, p->off, p->precision, p->smax, p->batch_policy, &p->batch, why);
+        rkl_status st = batch_create(p->desc, p->gc, p->off, p->precision, p->smax, p->batch_policy, p->batch_mode,
+                                     &p->batch, why);
         if (st != RKL_OK) return fail(st, why);
     }
     if (p->batch_mode == 1) {
@@ -244,17 +245,26 @@ static rkl_status select_batch_policy(rkl_plan_s* p, int policy) {
     return ensure_batch(p);
 }
 
-// Select the batched launch mode; a captured graph holds the old launch
-// sequence, so it is dropped.
+// Select the batched launch mode, which has its own tiles; a captured graph
+// holds the old launch sequence, so it is dropped.  If the mode cannot be had,
+// the plan keeps the old one.
 static rkl_status select_batch_mode(rkl_plan_s* p, int mode) {
     if (mode == p->batch_mode) return ensure_batch(p);
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) return hipfail(e, "mode sync");
     drop_graph(p);
-    const int old = p->batch_mode;
+    BatchPlan* const old = p->batch;
+    const int old_mode = p->batch_mode;
+    p->batch = nullptr;
     p->batch_mode = mode;
     rkl_status st = ensure_batch(p);
-    if (st != RKL_OK) p->batch_mode = old;
+    if (st == RKL_OK) {
+        batch_free(old);
+    } else {
+        batch_free(p->batch);
+        p->batch = old;
+        p->batch_mode = old_mode;
+    }
     return st;
 }
 
@@ -502,7 +512,7 @@ rkl_status rkl_plan(const rkl_grid_desc* grids, int32_t ngrids, const rkl_option
     if (e != hipSuccess) { free_plan(p); return hipfail(e, "plan upload"); }
     if (ngrids > 1 && o.scheme == RKL_RKL2) {
         std::string why;
-        rkl_status st = batch_create(p->desc, p->gc, p->off, p->precision, p->smax, 0, &p->batch, why);
+        rkl_status st = batch_create(p->desc, p->gc, p->off, p->precision, p->smax, 0, 0, &p->batch, why);
         if (st != RKL_OK) { free_plan(p); return fail(st, why); }
     }
     if (o.variant >= 0) {

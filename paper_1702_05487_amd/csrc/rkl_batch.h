@@ -23,9 +23,10 @@ struct BatchBuffers {
     GridState* state;      // ngrids
 };
 
-// policy: index into the batched tile policies (batch_policy_count())
+// policy: index into the batched tile policies (batch_policy_count()); mode:
+// the launch mode the tiles are for (see batch_launch)
 rkl_status batch_create(const std::vector<rkl_grid_desc>& desc, const std::vector<GridConst>& gc,
-                        const std::vector<int64_t>& off, int precision, int smax, int policy,
+                        const std::vector<int64_t>& off, int precision, int smax, int policy, int mode,
                         BatchPlan** out, std::string& why);
 int batch_policy_count();
 void batch_policy_info(int policy, int* half_rows, int* bz);

@@ -37,6 +37,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <numeric>
 
 #include "rkl_batch.h"
@@ -386,13 +387,15 @@ void batch_policy_info(int policy, int* half_rows, int* bz) {
     *bz = kPolicies[policy].bz;
 }
 
+static int chunks(int n2, int zmax) { return (n2 + zmax - 1) / zmax; }
+
 static void choose_tile(const GridConst& g, int policy, int plcap, int zmax, int& bx, int& by, int& bz) {
     const BatchPolicy& P = kPolicies[policy];
     bx = std::min(g.n0, 64);
     if (P.half_rows && g.n0 > 32) bx = std::min((g.n0 + 1) / 2, 32);
     by = std::min(std::min(g.n1, kBT / bx), 64);
     while (by > 1 && (bx + 2) * (by + 2) > plcap) --by;
-    const int nzc = (g.n2 + zmax - 1) / zmax;
+    const int nzc = chunks(g.n2, zmax);
     bz = (g.n2 + nzc - 1) / nzc;   // chunks of equal length, at most zmax planes
 }
 
@@ -407,22 +410,29 @@ static void choose_tile(const GridConst& g, int policy, int plcap, int zmax, int
 // Measured per batched super-step (s to 30), the policy's 32 planes against
 // the chunk taken here: 10 grids of 12 to 50 cells a side, mixed, 1293 -> 311 us;
 // 134 of 14 to 55 1795 -> 1314 us; 2000 of 16 to 64 16.8 -> 16.3 ms.
+// The persistent launch keeps the policy's chunk: an item of stage j waits for
+// every tile of its grid, so more and shorter tiles mean more waits (100 mixed
+// grids of 64^3, s 20: 9.1 ms with 32 planes, 12.8 ms with the chunks taken here;
+// 100 of 8^3 431 us, 1153 us).
 static int longest_chunk(const std::vector<GridConst>& gc, int policy, int plcap, bool f32) {
     static const double c32[] = {0.0, 1.2, 1.4, 1.65, 1.95}, c64[] = {0.0, 1.5, 2.0, 2.5};
     const double* c = f32 ? c32 : c64;
     const int per_cu = f32 ? 4 : 3;
-    int best = kPolicies[policy].bz, deepest = 1;
-    for (const GridConst& g : gc) deepest = std::max(deepest, g.n2);
+    std::map<int, int64_t> columns;   // tile columns by depth
+    for (const GridConst& g : gc) {
+        int bx, by, bz;
+        choose_tile(g, policy, plcap, kPolicies[policy].bz, bx, by, bz);
+        columns[g.n2] += (int64_t)((g.n0 + bx - 1) / bx) * ((g.n1 + by - 1) / by);
+    }
+    int best = kPolicies[policy].bz;
     double cost = INFINITY;
-    for (int z = std::min(best, deepest); z >= 1; z -= z > 8 ? 2 : 1) {
+    for (int z = std::min(best, columns.rbegin()->first); z >= 1; z -= z > 8 ? 2 : 1) {
         int64_t tiles = 0, work = 0;   // work: plane iterations of all tiles
         int longest = 1;
-        for (const GridConst& g : gc) {
-            int bx, by, bz;
-            choose_tile(g, policy, plcap, z, bx, by, bz);
-            const int64_t columns = (int64_t)((g.n0 + bx - 1) / bx) * ((g.n1 + by - 1) / by), nzc = (g.n2 + bz - 1) / bz;
-            tiles += columns * nzc;
-            work += columns * (g.n2 + 2 * nzc);
+        for (const auto& d : columns) {
+            const int nzc = chunks(d.first, z), bz = (d.first + nzc - 1) / nzc;
+            tiles += d.second * nzc;
+            work += d.second * (d.first + 2 * nzc);
             longest = std::max(longest, bz + 2);
         }
         const int64_t slots = 256 * per_cu;
@@ -440,7 +450,7 @@ static int longest_chunk(const std::vector<GridConst>& gc, int policy, int plcap
 }
 
 rkl_status batch_create(const std::vector<rkl_grid_desc>& desc, const std::vector<GridConst>& gc,
-                        const std::vector<int64_t>& off, int precision, int smax, int policy,
+                        const std::vector<int64_t>& off, int precision, int smax, int policy, int mode,
                         BatchPlan** out, std::string& why) {
     *out = nullptr;
     if (policy < 0 || policy >= batch_policy_count()) {
@@ -453,7 +463,7 @@ rkl_status batch_create(const std::vector<rkl_grid_desc>& desc, const std::vecto
     const int fycap = f32 ? Cap<float>::FY : Cap<double>::FY;
     const int n = (int)desc.size();
     std::vector<BatchGrid> h(n);
-    const int zmax = longest_chunk(gc, policy, plcap, f32);
+    const int zmax = mode == 1 ? kPolicies[policy].bz : longest_chunk(gc, policy, plcap, f32);
     int64_t items = 0;
     for (int g = 0; g < n; ++g) {
         if (desc[g].limiter != desc[0].limiter || desc[g].saturation != desc[0].saturation ||

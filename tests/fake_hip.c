@@ -85,7 +85,10 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t ld
     return OK;
 }
 
+size_t fake_alloc[4096];      /* sizes of the device allocations, in order */
+int fake_allocs = 0;
 hipError_t hipMalloc(void **p, size_t n) {
+    if (fake_allocs < 4096) fake_alloc[fake_allocs++] = n;
     if (fake_cap_bytes_on && n > fake_cap_bytes) { *p = NULL; return last = OUT_OF_MEMORY; }
     *p = aligned_alloc(256, (n + 255) / 256 * 256 + 256);   /* pages are touched only where written */
     return *p ? OK : (last = OUT_OF_MEMORY);

@@ -104,3 +104,27 @@ for n, prec, phys, blocks in CASES:
     assert got == blocks, (n, prec, phys)
     rkl.rkl_destroy(plan)
 ''')
+
+
+def test_persistent_batches_keep_the_chunk_of_the_policy(tmp_path):
+    """the per-stage launches shorten the chunks of a small batch, the persistent
+    launch does not; switching back and forth gives each its own tiles"""
+    fake_hip.run(tmp_path, r'''
+sizes = (ctypes.c_size_t * 4096).in_dll(hip, "fake_alloc")
+grids = [desc((32, 32, 64)) for _ in range(12)]
+for prec in (0, 1):
+    for policy in range(rkl.rkl_batch_policy_count()):
+        tz = rkl.rkl_batch_policy_info(policy)[1]
+        plan = rkl.rkl_plan(grids, precision=prec)
+        lib.rkl_set_batch_policy(plan, policy)
+
+        def items(mode):
+            put("allocs", 0)
+            assert lib.rkl_set_batch_mode(plan, mode) == 0
+            return sizes[1] // 8           # the second allocation is the list of (grid, tile) pairs
+        first = items(1)
+        assert first %% (12 * (-(-64 // tz))) == 0 and first // (12 * (-(-64 // tz))) <= 8, (policy, first)
+        hip.fake_reset()
+        assert items(0) > first and items(1) == first
+        rkl.rkl_destroy(plan)
+'''.replace("%%", "%"))
