@@ -50,7 +50,11 @@ struct rkl_plan_s {
     double* Yd = nullptr;
     // 1-D and 2-D grids (rkl_flat.h): their tilings, and three more fields of
     // the largest one that is cut into several regions
-    std::vector<FlatTiling> flat, flat_once;
+    struct Flat {
+        bool known = false;
+        FlatTiling t, once;
+    };
+    std::vector<Flat> flat;     // found on a grid's first use (flat_of)
     double* Fc = nullptr;       // the second pair of stage buffers (one allocation with Fd and Fz)
     double* Fd = nullptr;
     double* Fz = nullptr;       // copy of Y0
@@ -419,18 +423,30 @@ static rkl_status select_variant(rkl_plan_s* p, int v) {
     return RKL_OK;
 }
 
-// Tilings of the plan's 1-D and 2-D grids and the scratch of the several-stage
-// launches; where it cannot be allocated those grids run one stage a launch.
+// the tilings of a 1-D or 2-D grid, found on first use
+static const rkl_plan_s::Flat& flat_of(rkl_plan_s* p, int32_t g) {
+    rkl_plan_s::Flat& f = p->flat[g];
+    if (!f.known) {
+        f.known = true;
+        const GridConst& c = p->gc[g];
+        if (c.ndim <= 2 && p->off[g + 1] - p->off[g] <= kFlatMostCells) {
+            f.t = flat_tiling(p->precision, c);
+            f.once = flat_tiling_once(p->precision, c);
+        }
+    }
+    return f;
+}
+
+// Scratch of the several-stage launches of 1-D and 2-D grids: three fields of the
+// largest one cut into several regions (of many grids, of the largest).  Where it
+// cannot be allocated those grids run one stage a launch.
 static void make_flat(rkl_plan_s* p) {
     p->flat.resize(p->ngrids);
-    p->flat_once.resize(p->ngrids);
     int64_t most = 0;
     for (int g = 0; g < p->ngrids; ++g) {
         const int64_t n = p->off[g + 1] - p->off[g];
         if (p->gc[g].ndim > 2 || n > kFlatMostCells) continue;
-        p->flat[g] = flat_tiling(p->precision, p->gc[g]);
-        p->flat_once[g] = flat_tiling_once(p->precision, p->gc[g]);
-        if (p->flat[g].f && p->flat[g].blocks() > 1) most = std::max(most, n);
+        if (p->ngrids > 16 || flat_of(p, g).t.blocks() > 1) most = std::max(most, n);
     }
     if (!most) return;
     if (hipMalloc(&p->Fc, sizeof(double) * 3 * most) == hipSuccess) {
@@ -440,8 +456,6 @@ static void make_flat(rkl_plan_s* p) {
     }
     (void)hipGetLastError();
     p->Fc = nullptr;
-    for (auto& t : p->flat)
-        if (t.blocks() > 1) t = FlatTiling();
 }
 
 rkl_status rkl_plan(const rkl_grid_desc* grids, int32_t ngrids, const rkl_options* opt, rkl_plan_t* out) {
@@ -480,11 +494,22 @@ rkl_status rkl_plan(const rkl_grid_desc* grids, int32_t ngrids, const rkl_option
 
     const size_t rs = o.precision == RKL_MIXED ? sizeof(float) : sizeof(double);
     const std::vector<double> tab = coefficient_table(o.smax, o.scheme);
+    // the most workgroups of a one-stage launch; of a batch a bound that needs no
+    // fitting (a workgroup has 256 cells or, of a shortened tile, one plane of it)
     int64_t ext_blocks = 1;
-    for (int32_t g = 0; g < ngrids; ++g)
+    for (int32_t g = 0; g < ngrids; ++g) {
+        const GridConst& c = p->gc[g];
+        if (ngrids > 16) {
+            ext_blocks = std::max(ext_blocks, stage_blocks(Variant{kBlockX, kBlockY, kBlockZ, 1}, c));
+            ext_blocks = std::max(ext_blocks, stage_blocks(Variant{16, 16, 1, 1}, c));
+            ext_blocks = std::max(ext_blocks, stage_blocks(Variant{32, 8, 1, 1}, c));
+            ext_blocks = std::max(ext_blocks, stage_blocks(Variant{64, 4, 1, 1}, c));
+            continue;
+        }
         for (int v = 0; v < variant_count(); ++v)
             if (variant_get(v).fuse == 1)
-                ext_blocks = std::max(ext_blocks, stage_blocks(fit_variant(p->precision, variant_get(v), p->gc[g]), p->gc[g]));
+                ext_blocks = std::max(ext_blocks, stage_blocks(fit_variant(p->precision, variant_get(v), c), c));
+    }
     const auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t b_ok = up(sizeof(GridState) * ngrids), b_part = b_ok + up(sizeof(int32_t) * ngrids),
                  b_ext = b_part + up(sizeof(double) * 3 * 1024);
@@ -654,7 +679,11 @@ static rkl_status wait_host(rkl_plan_t p, hipStream_t st, HostWords* out) {
 // ------------------------------------------------- 1-D and 2-D grids ----
 // several stages per launch; while kernel timing records, one (the timing is
 // per stage launch)
-static bool use_flat(rkl_plan_t p, int32_t g) { return p->flat[g].f > 0 && !p->prof; }
+static bool use_flat(rkl_plan_t p, int32_t g) {
+    if (p->prof) return false;
+    const FlatTiling& t = flat_of(p, g).t;
+    return t.f > 0 && (t.blocks() == 1 || p->Fc);
+}
 
 // what the launches of a 1-D or 2-D grid share; every workgroup of the first
 // one forms the state
@@ -694,7 +723,7 @@ static rkl_status flat_group(rkl_plan_t p, int32_t g, FlatLaunch& P, int group, 
 static rkl_status flat_superstep_async(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_hyp, int32_t s_cap,
                                        int32_t* s_out, hipStream_t st) {
     FlatLaunch P;
-    if (rkl_status e = flat_start(p, g, p->flat[g], T, b, dt_hyp, 0, s_cap, &P, st)) return e;
+    if (rkl_status e = flat_start(p, g, flat_of(p, g).t, T, b, dt_hyp, 0, s_cap, &P, st)) return e;
     P.Tout = T;
     P.src.s_out = s_out;
     P.launches = flat_groups(P.t, s_cap);
@@ -711,9 +740,9 @@ rkl_status rkl_flux_div(rkl_plan_t p, int32_t g, const double* T, const void* b,
     if (!T || !b || !out) return fail(RKL_EINVAL, "NULL field pointer");
     if (out == T || (const void*)out == b) return fail(RKL_EINVAL, "out must not alias T or b");
     hipStream_t s = (hipStream_t)stream;
-    if (p->flat_once[g].f && !p->prof) {
+    if (!p->prof && flat_of(p, g).once.f) {
         FlatLaunch P;
-        if ((st = flat_start(p, g, p->flat_once[g], T, b, 0.0, 1, p->smax, &P, s)) != RKL_OK) return st;
+        if ((st = flat_start(p, g, flat_of(p, g).once, T, b, 0.0, 1, p->smax, &P, s)) != RKL_OK) return st;
         P.kind = 0;
         P.first = 1;
         P.Tout = out;
@@ -775,7 +804,7 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
     FlatLaunch P;
     if (use_flat(p, g)) {
         // group 0 finds its share of the stages from s
-        if ((st = flat_start(p, g, p->flat[g], T, b, dt_hyp, 0, p->smax, &P, s)) != RKL_OK) return st;
+        if ((st = flat_start(p, g, flat_of(p, g).t, T, b, dt_hyp, 0, p->smax, &P, s)) != RKL_OK) return st;
         P.Tout = T;
         P.s_even = p->smax + 1;
         P.src.host = p->host;
@@ -973,7 +1002,7 @@ static rkl_status euler_substeps(rkl_plan_t p, int32_t g, double* T, const void*
         P.Tout = T;
         P.b = b;
         P.state = p->state + g;
-        P.t = p->flat[g];
+        P.t = flat_of(p, g).t;
         P.gc = gc;
         const bool one = P.t.blocks() == 1;
         const int64_t f = std::min(P.t.f, kFlatEuler);

@@ -128,3 +128,45 @@ for prec in (0, 1):
         assert items(0) > first and items(1) == first
         rkl.rkl_destroy(plan)
 '''.replace("%%", "%"))
+
+
+def test_plan_of_many_grids_is_quick(tmp_path):
+    """host time of rkl_plan, a grid of a batch: 1.1 us before launches were fitted
+    to grids, 0.6 us now; fitting every variant to every grid took 3.4 us"""
+    fake_hip.run(tmp_path, r'''
+import random, time
+r = random.Random(1)
+for ndim in (3, 2):
+    grids = [desc((r.randint(16, 64), r.randint(16, 64), r.randint(16, 64) if ndim == 3 else 1), ndim) for _ in range(2000)]
+    best = 1e9
+    for _ in range(15):
+        t = time.perf_counter()
+        plan = rkl.rkl_plan(grids, smax=32)
+        best = min(best, time.perf_counter() - t)
+        rkl.rkl_destroy(plan)
+    assert best <= 2000 * 2e-6, (ndim, best)
+''')
+
+
+def test_extrema_of_a_batch_fit(tmp_path):
+    """the room for the last stage's extrema covers every variant's launch, also
+    where it is bounded instead of fitted (more than 16 grids)"""
+    fake_hip.run(tmp_path, r'''
+import random
+sizes = (ctypes.c_size_t * 4096).in_dll(hip, "fake_alloc")
+r = random.Random(2)
+for k in range(12):
+    ns = [tuple(r.choice((1, 2, 5, 17, 33, 64, 130, 200)) for _ in range(3)) for _ in range(17)]
+    for prec in (0, 1):
+        put("allocs", 0)
+        plan = rkl.rkl_plan([desc(n, law=(2.5, 1.7)[k % 2]) for n in ns], precision=prec)
+        room = sizes[4]                       # Ya, Yb, tau M(Y0), coefficients, then the small one
+        for v in list(range(8)) + [16]:
+            rkl.rkl_set_variant(plan, v)
+            for g in range(17):
+                hip.fake_reset()
+                rkl.rkl_supersteps_async(plan, g, T, b, 1e-3, 2, 3, None, None)
+                most = max(l[1] for l in launches() if "stage_kernel" in l[0] or "block_kernel" in l[0])
+                assert 24 * most <= room - 24 * 1024, (ns[g], v, most, room)
+        rkl.rkl_destroy(plan)
+''', 300)
