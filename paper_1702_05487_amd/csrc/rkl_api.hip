@@ -52,7 +52,7 @@ struct rkl_plan_s {
     // the largest one that is cut into several regions
     struct Flat {
         bool known = false;
-        FlatTiling t, once;
+        FlatTiling t, few, once;   // few: for super-steps of few stages (flat_is_few)
     };
     std::vector<Flat> flat;     // found on a grid's first use (flat_of)
     double* Fc = nullptr;       // the second pair of stage buffers (one allocation with Fd and Fz)
@@ -431,6 +431,7 @@ static const rkl_plan_s::Flat& flat_of(rkl_plan_s* p, int32_t g) {
         const GridConst& c = p->gc[g];
         if (c.ndim <= 2 && p->off[g + 1] - p->off[g] <= kFlatMostCells) {
             f.t = flat_tiling(p->precision, c);
+            f.few = flat_is_few(c, 1) ? flat_tiling(p->precision, c, true) : f.t;
             f.once = flat_tiling_once(p->precision, c);
         }
     }
@@ -685,6 +686,11 @@ static bool use_flat(rkl_plan_t p, int32_t g) {
     return t.f > 0 && (t.blocks() == 1 || p->Fc);
 }
 
+// the tiling for that many stages
+static const FlatTiling& flat_for(rkl_plan_t p, int32_t g, int64_t stages) {
+    return flat_is_few(p->gc[g], stages) ? flat_of(p, g).few : flat_of(p, g).t;
+}
+
 // what the launches of a 1-D or 2-D grid share; every workgroup of the first
 // one forms the state
 static rkl_status flat_start(rkl_plan_t p, int32_t g, const FlatTiling& t, const double* T, const void* b,
@@ -723,7 +729,7 @@ static rkl_status flat_group(rkl_plan_t p, int32_t g, FlatLaunch& P, int group, 
 static rkl_status flat_superstep_async(rkl_plan_t p, int32_t g, double* T, const void* b, double dt_hyp, int32_t s_cap,
                                        int32_t* s_out, hipStream_t st) {
     FlatLaunch P;
-    if (rkl_status e = flat_start(p, g, flat_of(p, g).t, T, b, dt_hyp, 0, s_cap, &P, st)) return e;
+    if (rkl_status e = flat_start(p, g, flat_for(p, g, s_cap), T, b, dt_hyp, 0, s_cap, &P, st)) return e;
     P.Tout = T;
     P.src.s_out = s_out;
     P.launches = flat_groups(P.t, s_cap);
@@ -831,6 +837,9 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
     if (use_flat(p, g)) {
         P.launches = flat_groups(P.t, S);
         P.s_even = 0;
+        // the second of two groups can be cut for its own few stages
+        const FlatTiling& t = flat_for(p, g, S);
+        if (P.launches == 2 && t.f >= S / 2) P.t = t;
         for (int k = 1; k < P.launches; ++k)
             if ((st = flat_group(p, g, P, k, s)) != RKL_OK) return st;
         undo.on = false;
@@ -1002,22 +1011,26 @@ static rkl_status euler_substeps(rkl_plan_t p, int32_t g, double* T, const void*
         P.Tout = T;
         P.b = b;
         P.state = p->state + g;
-        P.t = flat_of(p, g).t;
+        // one or two sub-steps of a large 2-D grid: a launch each, regions for one
+        const bool each = count <= 2 && flat_is_few(gc, count);
+        P.t = each ? flat_of(p, g).once : flat_for(p, g, count);
         P.gc = gc;
         const bool one = P.t.blocks() == 1;
         const int64_t f = std::min(P.t.f, kFlatEuler);
         int64_t groups = (count + f - 1) / f;
-        if (!one && groups < 2) groups = 2;
+        const bool copy = each && groups == 1;   // cheaper than a launch without a sub-step
+        if (!one && groups < 2 && !copy) groups = 2;
         for (int64_t k = 0; k < groups; ++k) {
             const int64_t c0 = count * k / groups, c1 = count * (k + 1) / groups;
             P.first = one || k == 0;
-            P.last = one || k == groups - 1;
+            P.last = one || (k == groups - 1 && !copy);
             P.count = (int)(c1 - c0);
             for (int64_t i = c0; i < c1; ++i) P.scale[i - c0] = -tau(i) * gc.fac;
             P.out1 = k % 2 == 0 ? A : p->Fc;
             P.in1 = k % 2 == 0 ? p->Fc : A;
             HIPCHECK(launch_flat(p->precision, P, s), "sub-step launch");
         }
+        if (copy) HIPCHECK(hipMemcpyAsync(T, A, sizeof(double) * n, hipMemcpyDeviceToDevice, s), "result copy");
         return RKL_OK;
     }
     for (int64_t k = 0; k < count; ++k) {

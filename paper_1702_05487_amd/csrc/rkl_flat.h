@@ -39,8 +39,17 @@ struct FlatTiling {
     int threads = 0;
     int blocks() const { return nt0 * nt1; }
 };
-// the tiling for grid gc (1-D or 2-D), or f = 0 where one launch per stage is used
-FlatTiling flat_tiling(int precision, const GridConst& gc);
+// the tiling for grid gc (1-D or 2-D), or f = 0 where one launch per stage is used;
+// few: for super-steps of at most kFewStages
+FlatTiling flat_tiling(int precision, const GridConst& gc, bool few = false);
+// Stage counts with a tiling of their own on 2-D grids of 2^16 cells and more: the
+// ordinary one reaches f cells around each tile, which pays from about five stages
+// on.  s = 3, us a super-step, one stage a launch / ordinary / few: 2048^2 mixed
+// (kappa0) 305 / 338 / 250, mixed T^1.7 396 / 458 / 406, FP64 T^2.5 450 / 355 / 303.
+constexpr int kFewStages = 4;
+inline bool flat_is_few(const GridConst& gc, int64_t stages) {
+    return gc.ndim == 2 && stages <= kFewStages && (int64_t)gc.n0 * gc.n1 >= 65536;
+}
 // the tiling of a single operator evaluation
 FlatTiling flat_tiling_once(int precision, const GridConst& gc);
 // groups of a super-step of s stages

@@ -20,14 +20,15 @@ namespace rkl {
 // Measured per super-step against one stage per launch: 400 cells (s = 20)
 // 120 -> 17 us, 64 x 64 (14) 85 -> 23 us, 200 x 200 MC (20) 130 -> 42 us;
 // 1024 x 1024 mixed, MC and saturation, 34.7 -> 18.3 us per stage.
-static double flat_cost(int precision, const GridConst& gc, const FlatTiling& t) {
+// (2 with `few`: two groups of at most two stages.)
+static double flat_cost(int precision, const GridConst& gc, const FlatTiling& t, bool few) {
     const bool f32 = precision == RKL_MIXED, sat = gc.saturation != 0, lim = gc.limiter != 0;
     const bool km1 = gc.kmode == 1, km2 = gc.kmode == 2, two = gc.ndim == 2;
     const double face = !two ? (f32 ? 0.04 + 0.03 * sat : 0.05 + 0.05 * sat) + (km2 ? 0.2 : 0.0)
                         : f32 ? 2 * (0.05 + 0.03 * lim + 0.05 * sat + 0.03 * km1 + 0.1 * km2)
                               : 2 * (0.08 + 0.03 * lim + 0.08 * sat + 0.06 * km1 + 0.3 * km2);
     const double setup = two ? 4.0 : 2.2;
-    const int f = t.blocks() == 1 ? 24 : std::min(t.f, two ? 10 : 14);
+    const int f = t.blocks() == 1 ? 24 : std::min(t.f, few ? 2 : two ? 10 : 14);
     const int waves = t.threads / 64, per_cu = std::max(1, 16 / waves);
     const int64_t nb = t.blocks(), slots = 256 * per_cu, full = nb / slots, rem = nb % slots;
     const auto round = [&](int64_t wgs) { return setup + f * (0.45 + face * ((wgs * waves + 3) / 4)); };
@@ -58,14 +59,14 @@ static FlatTiling shape(const GridConst& gc, int w, int h, int f) {
     return t;
 }
 
-FlatTiling flat_tiling(int precision, const GridConst& gc) {
+FlatTiling flat_tiling(int precision, const GridConst& gc, bool few) {
     FlatTiling best;
     if (gc.ndim > 2 || gc.n2 != 1) return best;
     double cost = INFINITY;
     const auto take = [&](int w, int h, int f) {
         const FlatTiling t = shape(gc, w, h, f);
         if (!t.f) return;
-        const double c = flat_cost(precision, gc, t);
+        const double c = flat_cost(precision, gc, t, few);
         if (c < cost) {
             cost = c;
             best = t;

@@ -100,7 +100,7 @@ extern "C" rkl_status rkl_superstep_noalloc(const rkl_grid_desc* grid, int32_t p
     const GridConst gc = make_const(*grid, RKL_RKL2);
     // 1-D and 2-D grids: several stages per launch (rkl_flat.h), where the
     // array holds the three further fields of a grid cut into several regions
-    const FlatTiling ft = grid->ndim <= 2 ? flat_tiling(precision, gc) : FlatTiling();
+    const FlatTiling ft = grid->ndim <= 2 ? flat_tiling(precision, gc, flat_is_few(gc, s_cap)) : FlatTiling();
     if (ft.f && (ft.blocks() == 1 || 2 * N <= kCells)) {
         FlatLaunch P = FlatLaunch();
         double* f = (double*)base;   // five fields, then tau M(Y0)

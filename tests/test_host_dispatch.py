@@ -170,3 +170,23 @@ for k in range(12):
                 assert 24 * most <= room - 24 * 1024, (ns[g], v, most, room)
         rkl.rkl_destroy(plan)
 ''', 300)
+
+
+def test_few_stages_of_a_large_2d_grid(tmp_path):
+    """one sub-step takes one launch (and a copy), two take two; a super-step of few
+    stages takes regions that reach fewer cells around their tiles"""
+    fake_hip.run(tmp_path, r'''
+plan = rkl.rkl_plan([desc((1000, 1000, 1), 2, sat=2, law=1.7)], precision=1)
+flat = lambda: [l for l in launches() if "flat_kernel" in l[0]]
+for q in (1, 2):
+    hip.fake_reset()
+    assert rkl.rkl_subcycle(plan, 0, T, b, q - 0.5, 9, None) == q
+    assert len(flat()) == q, flat()
+plan = rkl.rkl_plan([desc((2048, 2048, 1), 2, lim=0, law=0.0)], precision=1)
+cells = {}
+for cap in (3, 20):
+    hip.fake_reset()
+    rkl.rkl_superstep_async(plan, 0, T, b, 1e-3, cap, None, None)
+    cells[cap] = flat()[0][1] * flat()[0][2] / 2048.0 ** 2      # computed, borders included
+assert cells[3] < 1.45 < 1.6 < cells[20], cells
+''')
