@@ -733,7 +733,7 @@ static rkl_status flat_superstep_async(rkl_plan_t p, int32_t g, double* T, const
     P.Tout = T;
     P.src.s_out = s_out;
     P.launches = flat_groups(P.t, s_cap);
-    P.s_even = flat_even_from(P.t, P.launches);
+    P.s_even = flat_even_from(P.t, P.launches, P.smin);
     for (int k = 0; k < P.launches; ++k)
         if (rkl_status e = flat_group(p, g, P, k, st, flat_asks(P.t, k))) return e;
     return RKL_OK;
@@ -836,7 +836,6 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
                                      ", smax=" + std::to_string(p->smax) + "]");
     if (use_flat(p, g)) {
         P.launches = flat_groups(P.t, S);
-        P.s_even = 0;
         // the second of two groups can be cut for its own few stages
         const FlatTiling& t = flat_for(p, g, S);
         if (P.launches == 2 && t.f >= S / 2) P.t = t;

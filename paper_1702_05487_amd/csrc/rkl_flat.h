@@ -63,9 +63,9 @@ __host__ __device__ inline int flat_groups(const FlatTiling& t, int s) {
 // its stages evenly over all of them while they are at most twice what it needs
 // (one without stages costs about as much as the set-up of one with few), that
 // is from this s on; below it is cut into the groups it needs.
-inline int flat_even_from(const FlatTiling& t, int launches) {
+inline int flat_even_from(const FlatTiling& t, int launches, int smin) {
     const int half = (launches + 1) / 2;
-    return half <= 2 ? 0 : t.f * (half - 1) + 1;
+    return half <= 2 ? smin : t.f * (half - 1) + 1;
 }
 
 // Super-steps with s on the device: whether launch `group` asks for s before it
@@ -87,10 +87,10 @@ struct FlatLaunch {
     const void* b;
     GridState* state;
     const double* coef;  // RKL table, row (s, j) at 5 (s(s+1)/2 + j); NULL: RKL2 rows formed here
-    int group;
-    int launches;        // groups of a super-step of s >= s_even stages; of fewer: flat_groups(t, s),
-    int s_even;          // and later launches do nothing
-    int smin, s_cap;     // s outside [smin, s_cap]: nothing is done
+    int group;           // nothing is done from state->groups on, which group 0 stores:
+    int launches;        // `launches` from s_even stages on, else flat_groups(t, s);
+    int s_even;
+    int smin, s_cap;     // 0 where s is outside [smin, s_cap]
     FlatTiling t;
     GridConst gc;
     int derive;          // every workgroup forms the state from src; else *state holds it

@@ -45,13 +45,10 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     static_assert(kFlatThreads <= 16 * 64, "a slot of red per wave");
     __shared__ GridState sst;
     const FlatTiling& t = P.t;
-    if (ASK) {
-        const int sa = P.state->s;
-        if (sa > P.s_cap || (sa < P.s_even && P.group >= flat_groups(t, sa))) return;
-    }
+    if (ASK && P.group >= P.state->groups) return;
     const int tid = threadIdx.x, nt = blockDim.x;
     // the state as a former launch left it (the group that forms it does not use these)
-    int s = P.state->s;
+    int s = P.state->s, G = P.state->groups;
     double tref = P.state->tref, cdiv = P.state->cdiv;
     const int n0 = P.gc.n0, n1 = P.gc.n1;
     const bool ox = P.gc.bc & 1, oy = P.gc.bc & 2, fx = P.gc.fixed & 1, fy = P.gc.fixed & 2;
@@ -162,11 +159,12 @@ __global__ __launch_bounds__(kFlatThreads) void flat_kernel(FlatLaunch P) {
     bool last = true;
     double scale = -P.gc.fac;
     if (P.kind == 1) {
-        if (s < P.smin || s > P.s_cap) return;   // uniform over the launch
-        int G = P.launches;
-        if (s < P.s_even) {
-            G = flat_groups(t, s);
-            if (P.group >= G) return;
+        if (P.derive) {
+            if (s < P.smin || s > P.s_cap) return;   // uniform over the launch; groups stays 0
+            G = s >= P.s_even ? P.launches : flat_groups(t, s);
+            if (blockIdx.x == 0 && tid == 0) P.state->groups = G;
+        } else if (P.group >= G) {
+            return;
         }
         j0 = (int)(((unsigned)s * P.group + G - 1) / G) + 1;
         j1 = (int)(((unsigned)s * (P.group + 1) + G - 1) / G);

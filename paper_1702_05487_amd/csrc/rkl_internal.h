@@ -14,6 +14,7 @@ struct GridState {
     double tref;     // reference temperature subtracted before FP32 flux arithmetic
     double tmax, tmin;
     int32_t s;       // RKL2 stage count (0 when not a super-step)
+    int32_t groups;  // launches that the stages of a 1-D or 2-D super-step are cut into
     uint32_t flags;  // RKL_FLAG_* bits
 };
 
@@ -73,6 +74,7 @@ __device__ inline GridState finalize_state(const GridConst& g, double mx, double
     o.tmax = mx;
     o.tmin = mn;
     o.s = s;
+    o.groups = 0;
     o.flags = flags;
     return o;
 }

@@ -112,7 +112,7 @@ extern "C" rkl_status rkl_superstep_noalloc(const rkl_grid_desc* grid, int32_t p
         P.b = b;
         P.state = state;
         P.launches = flat_groups(ft, s_cap);
-        P.s_even = flat_even_from(ft, P.launches);
+        P.s_even = flat_even_from(ft, P.launches, 2);
         P.smin = 2;
         P.s_cap = s_cap;
         P.t = ft;
