@@ -218,15 +218,18 @@ rkl_status rkl_superstep(rkl_plan_t plan, int32_t grid, double *T, const void *b
  * rkl_superstep_async: the RKL2 super-step of rkl_superstep (Appendix A, Eq.
  * rkl2scheme; s from Eq. RKL-s) with no host synchronisation and no
  * allocation, so it can be captured in a HIP graph.  s is computed on the
- * device and never read back: the call enqueues one reduction, one finalize
- * launch and s_cap stage launches; stage j does nothing when j > s.  If
- * s > s_cap, every stage does nothing (T unchanged) and the grid is flagged
- * RKL_FLAG_STAGES (rkl_query).  s_out: device int32 (may be NULL) receiving
+ * device and never read back: the call enqueues a reduction (not for fields of
+ * up to 16384 cells), and on 3-D grids one finalize launch and s_cap stage
+ * launches, on 1-D and 2-D ones a launch per group of stages that s_cap allows.
+ * A launch whose stages are all beyond s does nothing.  If s > s_cap, every
+ * launch does nothing (T unchanged) and the grid is flagged RKL_FLAG_STAGES
+ * (rkl_query).  s_out: device int32 (may be NULL) receiving
  * s.  s_cap in [2, the plan's smax] (RKL_EINVAL otherwise); RKL2 plans only
  * (RKL_EINVAL for RKL1).  Uses the plan's one-stage stencil variant (variant
  * 0 while a two-stage variant is selected); the same bits as rkl_superstep
  * for the same variant.  An empty stage launch costs a few microseconds, so
- * s_cap should be near the largest s expected.
+ * s_cap should be near the largest s expected; on 1-D and 2-D grids up to about
+ * twice s costs little.
  */
 rkl_status rkl_superstep_async(rkl_plan_t plan, int32_t grid, double *T, const void *b, double dt_hyp,
                                int32_t s_cap, int32_t *s_out, void *stream);
@@ -255,8 +258,9 @@ rkl_status rkl_supersteps_async(rkl_plan_t plan, int32_t grid, double *T, const 
 /*
  * rkl_superstep_noalloc: for callers that cannot allocate device memory --
  * code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  The super-step of rkl_superstep_async (RKL2, s on the device,
- * s_cap stage launches, no host synchronisation) on one grid described by
+ * hipMalloc.  The super-step of rkl_superstep_async (RKL2, s on the device, the
+ * launches of s_cap, no host synchronisation; 2-D grids of more than 2^20 cells
+ * run one stage per launch) on one grid described by
  * *grid, with no plan and no allocation of any kind: its scratch is a static
  * device array inside the library, 8 B x 3 x RKL_NOALLOC_MAX_CELLS plus a
  * few KB (50.4 MB), held by each GPU the library runs on until the process
