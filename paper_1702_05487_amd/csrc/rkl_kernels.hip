@@ -122,11 +122,13 @@ static hipError_t launch_prec(const StageLaunch& P, int nblocks, const Variant& 
 // 256 CUs, long ones keep the two extra iterations and the halo planes cheap.
 // The last, partly filled round is priced half by its share of the slots and half
 // as a round of its own: workgroups of different rounds overlap, but not fully.
+// Several rounds end 0.15 of a march late (256^3, kappa0, chunks of 64 / 32 planes:
+// FP64 241 / 227 us a stage, mixed 175 / 165; with T^2.5 259 / 259 and 170 / 170).
 //
 // Blocks of 16 x 4 x 4 cells (rkl_block.h) have no march; n of them take
 // max(least, b0 + b1 n) microseconds.  The march's own time for the comparison is
 // start + (bz + lead) x rounds with it[k] an iteration and `mix` of the last
-// round as its own.  start to b1 are fits to 27 sizes from 8 x 8 x 512 to 384^3,
+// round as its own.  start to b1 are fits to 34 sizes from 8 x 8 x 512 to 2^22 cells,
 // every chunk, with the kernels as they are now (rms 2 to 5 %; FP64 without
 // saturation 9 %).  Beyond 2^22 cells the memory sets the time of both, and the
 // march reads less of it.  FP64 with pow() marches at one wave per SIMD (its
@@ -188,7 +190,8 @@ Variant fit_variant(int precision, Variant v, const GridConst& gc) {
         const int nzc = (gc.n2 + z - 1) / z;
         const int bz = (gc.n2 + nzc - 1) / nzc;   // chunks of equal length
         if (bz != z) continue;
-        const double cost = (bz + 2) * rounds(tiles * nzc, p.chunk, 0.5);
+        const int64_t nb = tiles * nzc;
+        const double cost = (bz + 2) * (rounds(nb, p.chunk, 0.5) + (nb < slots ? 0.0 : 0.15));
         if (cost < best_cost) {
             best_cost = cost;
             best = bz;
