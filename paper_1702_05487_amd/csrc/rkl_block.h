@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void block_kernel(StageLaunch P) {
         r0 = ld(b0, r); r1 = ld(b1, r); r2 = ld(b2, r);
         l0 = ld(b0, l); l1 = ld(b1, l); l2 = ld(b2, l);
     }
-    if (!stage_args(P, true, [&] { return s; }, [&] { return cdiv; }, a)) return;
+    if (!stage_args<true>(P, true, s, cdiv, a)) return;
     const FaceK<R> fk = make_facek<R>(P.kappa0, P.kexp, P.kperp, P.satq, tref);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {

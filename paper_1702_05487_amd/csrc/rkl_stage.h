@@ -34,24 +34,25 @@ __device__ __forceinline__ void stage_inputs(const StageLaunch& P, TileArgs& a) 
     a.Ym2 = j == 2 ? a.Yout : (j & 1) ? P.route.A : P.route.B;   // Y_{j-2} sits where Y_j goes
 }
 
-// The buffers and the coefficients of this launch, with s and cdiv of the
-// grid's state (get_s, get_cdiv: asked for where they are needed, since each wait
-// for a scalar at the start of a kernel costs 0.3 to 0.5 us); false where a
-// routed stage does nothing, uniform over the grid.  ext_able: the kernel can
-// keep the extrema of the last stage.
-template <typename S, typename C>
-__device__ __forceinline__ bool stage_args(const StageLaunch& P, bool ext_able, S get_s, C get_cdiv, TileArgs& a) {
+// The buffers and the coefficients of this launch, with s and cdiv of the grid's
+// state; false where a routed stage does nothing, uniform over the grid.
+// ext_able: the kernel can keep the extrema of the last stage.  EARLY (block
+// kernel): stage_inputs has been called and the state been asked for (s, cdiv);
+// else they are asked for here, where they are needed, since each wait for a
+// scalar at the start of a kernel costs 0.3 to 0.5 us.
+template <bool EARLY>
+__device__ __forceinline__ bool stage_args(const StageLaunch& P, bool ext_able, int s, double cdiv, TileArgs& a) {
     if (a.kind == 0) {
         a.scale = -P.fac;
     } else if (a.kind == 3) {
         a.scale = P.sub_scale;
     } else {
-        const int s = get_s();
+        if (!EARLY) s = P.state->s;
         if (P.route.A) {
             // the stage sequence was launched up to s_cap without knowing s
             const int j = P.stage;
             if (j > s || s < P.route.s_min || s > P.route.s_cap) return false;
-            stage_inputs(P, a);
+            if (!EARLY) stage_inputs(P, a);
             // Y_s goes to T, but not from stage 1, which reads T around each cell
             if (j < s || j == 1) a.Yout = (j & 1) ? P.route.A : P.route.B;
             a.ext = ext_able && P.ext.part && j == s;
@@ -62,7 +63,7 @@ __device__ __forceinline__ bool stage_args(const StageLaunch& P, bool ext_able, 
         a.omn = cf[2];
         a.mut = cf[3];
         a.gt = cf[4];
-        a.scale = -get_cdiv();
+        a.scale = -(EARLY ? cdiv : P.state->cdiv);
     }
     return true;
 }
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(BX* BY) void stage_kernel(StageLaunch P) {
     a.z1 = min(a.z0 + P.bz, a.n2);
     const double tref = sizeof(R) == 4 ? P.state->tref : 0.0;
     constexpr bool FIX = MODE == 1 || MODE == 3;
-    if (!stage_args(P, FIX, [&] { return P.state->s; }, [&] { return P.state->cdiv; }, a)) return;
+    if (!stage_args<false>(P, FIX, 0, 0.0, a)) return;
     const FaceK<R> fk = make_facek<R>(P.kappa0, P.kexp, P.kperp, P.satq, tref);
     if constexpr (FIX) {
         using PF = typename std::conditional<three_waves<R, BX, BY>(SAT, KM), Prefetch<1, 1, 0, true>,
