@@ -123,8 +123,9 @@ static hipError_t launch_prec(const StageLaunch& P, int nblocks, const Variant& 
 // The last, partly filled round is priced half by its share of the slots and half
 // as a round of its own: workgroups of different rounds overlap, but not fully.
 // Two rounds and more of the classical flux, which loads more than it computes, end
-// 0.15 of a march late (256^3, kappa0, chunks of 64 / 32 planes: FP64 241 / 227 us a
-// stage, mixed 175 / 165; with T^2.5 259 / 259 and 170 / 170).
+// 0.15 of a march late, between one and two rounds a share of that (256^3, kappa0,
+// chunks of 64 / 32 planes: FP64 241 / 227 us a stage, mixed 175 / 165; with T^2.5
+// 259 / 259 and 170 / 170; 176^3 FP64, T^2.5, 26 / 16 planes: 99 / 96).
 //
 // Blocks of 16 x 4 x 4 cells (rkl_block.h) have no march; n of them take
 // max(least, b0 + b1 n) microseconds.  The march's own time for the comparison is
@@ -192,7 +193,8 @@ Variant fit_variant(int precision, Variant v, const GridConst& gc) {
         const int bz = (gc.n2 + nzc - 1) / nzc;   // chunks of equal length
         if (bz != z) continue;
         const int64_t nb = tiles * nzc;
-        const double cost = (bz + 2) * (rounds(nb, p.chunk, 0.5) + (pow_law || sat || nb < 2 * slots ? 0.0 : 0.15));
+        const double late = pow_law || sat ? 0.0 : 0.15 * std::min(1.0, std::max(0.0, (double)nb / slots - 1.0));
+        const double cost = (bz + 2) * (rounds(nb, p.chunk, 0.5) + late);
         if (cost < best_cost) {
             best_cost = cost;
             best = bz;
