@@ -691,6 +691,17 @@ static const FlatTiling& flat_for(rkl_plan_t p, int32_t g, int64_t stages) {
     return flat_is_few(p->gc[g], stages) ? flat_of(p, g).few : flat_of(p, g).t;
 }
 
+// Whether rkl_superstep learns s before it launches a group.  pow() makes the border
+// of the ordinary tiling dear where a super-step turns out to have few stages, and
+// in mixed precision dearer than a launch a stage: s = 3 of mixed T^1.7, us, one
+// stage a launch / group 0 ahead of s / behind it: 1500 x 2100 319 / 360 / 317, 2048^2
+// 406 / 462 / 419, 4096^2 1584 / 1795 / 1580.  Other super-steps pay 7 us for the wait
+// (s = 5, 1500 x 2100: 512 / 462 / 470), too much below 2^21 cells.
+static bool flat_waits(rkl_plan_t p, int32_t g) {
+    const GridConst& gc = p->gc[g];
+    return gc.kmode == 2 && p->precision == RKL_MIXED && gc.ndim == 2 && (int64_t)gc.n0 * gc.n1 >= (int64_t)1 << 21;
+}
+
 // what the launches of a 1-D or 2-D grid share; every workgroup of the first
 // one forms the state
 static rkl_status flat_start(rkl_plan_t p, int32_t g, const FlatTiling& t, const double* T, const void* b,
@@ -814,7 +825,12 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
         P.Tout = T;
         P.s_even = p->smax + 1;
         P.src.host = p->host;
-        if ((st = flat_group(p, g, P, 0, s)) != RKL_OK) return st;
+        if (flat_waits(p, g)) {
+            HIPCHECK(launch_finalize(gc, P.src, gs, nullptr, s), "finalize launch");
+            P.src.host = nullptr;
+        } else if ((st = flat_group(p, g, P, 0, s)) != RKL_OK) {
+            return st;
+        }
     } else {
         // stage 1, and stage 2 unless it may be part of a fused launch or is timed
         StateSource q;
@@ -835,11 +851,13 @@ rkl_status rkl_superstep(rkl_plan_t p, int32_t g, double* T, const void* b, doub
         return fail(RKL_ESTAGES, "stage count " + std::to_string(S) + " outside [" + std::to_string(smin) +
                                      ", smax=" + std::to_string(p->smax) + "]");
     if (use_flat(p, g)) {
+        const FlatTiling& t = flat_for(p, g, S);
+        const bool all = flat_waits(p, g);   // no group is on its way
+        if (all) P.t = t;
         P.launches = flat_groups(P.t, S);
         // the second of two groups can be cut for its own few stages
-        const FlatTiling& t = flat_for(p, g, S);
         if (P.launches == 2 && t.f >= S / 2) P.t = t;
-        for (int k = 1; k < P.launches; ++k)
+        for (int k = all ? 0 : 1; k < P.launches; ++k)
             if ((st = flat_group(p, g, P, k, s)) != RKL_OK) return st;
         undo.on = false;
         return RKL_OK;

@@ -190,3 +190,23 @@ for cap in (3, 20):
     cells[cap] = flat()[0][1] * flat()[0][2] / 2048.0 ** 2      # computed, borders included
 assert cells[3] < 1.45 < 1.6 < cells[20], cells
 ''')
+
+
+def test_few_stages_of_a_large_mixed_pow_grid(tmp_path):
+    """kappa ~ T^1.7 in mixed precision: rkl_superstep learns s before it cuts a large
+    2-D grid, so that few stages get regions of their own in every group (a super-step
+    of three stages took 4 to 10 % longer than with one stage a launch)"""
+    fake_hip.run(tmp_path, r'''
+for n in ((1500, 1400, 1), (4096, 4096, 1)):
+    for prec, law in ((1, 1.7), (1, 2.5), (0, 1.7)):
+        plan = rkl.rkl_plan([desc(n, 2, law=law)], precision=prec)
+        for s in (3, 4, 5, 20):
+            put("s", s)
+            hip.fake_reset()
+            assert rkl.rkl_superstep(plan, 0, T, b, 1e-3, None) == s
+            flat = [l[1:] for l in launches() if "flat_kernel" in l[0]]
+            assert any("finalize" in l[0] for l in launches()) == (prec == 1 and law == 1.7)
+            if prec == 1 and law == 1.7:
+                assert len(set(flat)) == 1 and len(flat) >= 2, (n, s, flat)
+        rkl.rkl_destroy(plan)
+''')
